@@ -1313,6 +1313,7 @@ struct TableProblem {
     fas_grid* g;
     int T;                  // tile levels 0..T-1, tail from level T
     int height;             // levels below the finest (L)
+    bool tail_big;          // the tail takes the big LDS planes
     size_t tile_bytes;
     int blocks[3][fas::kMaxLevels];  // blocks of pre, first-cycle pre and post launches per level
     char* host;             // staging of the descriptors (pinned)
@@ -1357,7 +1358,7 @@ void build_table_problem(TableProblem& P, const void* rhs, void* u, int nu1, int
                                              l == 0 ? u : F.u, C.u, nullptr, nullptr,
                                              l == 0 ? g->partials : nullptr, act, base + (size_t)(3 * l + 2) * tb);
     }
-    fas::fill_tail_desc(g, P.T, g->coef, nu1, nu2, first, g->lev[P.T].u, g->lev[P.T].f, true, act, d.data() + 256);
+    P.tail_big = fas::fill_tail_desc(g, P.T, g->coef, nu1, nu2, first, g->lev[P.T].u, g->lev[P.T].f, true, act, d.data() + 256);
     fas::StatusDesc sd{};
     sd.partials = g->partials;
     sd.fpartials = g->fpartials;
@@ -1435,7 +1436,8 @@ int solve_table_impl(int nprob, fas_grid* const* grids, double dt, const fas_kap
     }
     // launch lists per height (pre, first-cycle pre, post) and tails per height
     typedef std::vector<std::pair<const void*, int>> Items;
-    std::vector<Items> pre((size_t)hmax + 1), pre1((size_t)hmax + 1), post((size_t)hmax + 1), tail((size_t)hmax + 1);
+    std::vector<Items> pre((size_t)hmax + 1), pre1((size_t)hmax + 1), post((size_t)hmax + 1);
+    std::vector<Items> tail[2] = {std::vector<Items>((size_t)hmax + 1), std::vector<Items>((size_t)hmax + 1)};
     Items status;
     for (const TableProblem& Q : P) {
         for (int l = 0; l < Q.T; ++l) {
@@ -1444,7 +1446,7 @@ int solve_table_impl(int nprob, fas_grid* const* grids, double dt, const fas_kap
             pre1[h].push_back({Q.tile(l == 0 ? 1 : 0, l), Q.blocks[1][l]});
             post[h].push_back({Q.tile(2, l), Q.blocks[2][l]});
         }
-        tail[(size_t)(Q.height - Q.T)].push_back({Q.tail(), 1});
+        tail[Q.tail_big ? 1 : 0][(size_t)(Q.height - Q.T)].push_back({Q.tail(), 1});
         status.push_back({Q.status(), 1});
     }
     const int first = (lead->dim + 1) & 1;
@@ -1459,8 +1461,10 @@ int solve_table_impl(int nprob, fas_grid* const* grids, double dt, const fas_kap
             for_chunks(k == 1 ? pre1[(size_t)h] : pre[(size_t)h], [&](const fas::TableLaunch& t, size_t) {
                 fas::launch_tile_table(stream, dtype, false, nu1, first, kv, wv, t);
             });
-            for_chunks(tail[(size_t)h],
-                       [&](const fas::TableLaunch& t, size_t) { fas::launch_tail_table(stream, dtype, 2, kv, t); });
+            for (int big = 0; big < 2; ++big)
+                for_chunks(tail[big][(size_t)h], [&](const fas::TableLaunch& t, size_t) {
+                    fas::launch_tail_table(stream, dtype, kv, big != 0, t);
+                });
         }
         for (int h = 0; h <= hmax; ++h)
             for_chunks(post[(size_t)h], [&](const fas::TableLaunch& t, size_t) {

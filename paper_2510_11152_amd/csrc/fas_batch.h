@@ -52,11 +52,12 @@ void launch_tile_table(hipStream_t stream, int dtype, bool post, int nu, int fir
 
 // ---- persistent coarse tails (kernels_tail.hip) -----------------------------------------
 size_t tail_desc_bytes(int dtype);
-// Descriptor of the tail of g from level `top` (as launch_tail), into host memory `out`.
-void fill_tail_desc(const fas_grid* g, int top, const Coef* coef, int pre, int post, int first, void* u, const void* r,
+// Descriptor of the tail of 2D grid g from level `top` (as launch_tail), into host memory
+// `out`; returns whether its launch takes the big LDS planes (kernels_tail.hip).
+bool fill_tail_desc(const fas_grid* g, int top, const Coef* coef, int pre, int post, int first, void* u, const void* r,
                     bool form_rhs, const int* act, void* out);
-// One workgroup per problem of t.
-void launch_tail_table(hipStream_t stream, int dtype, int dim, bool kv, const TableLaunch& t);
+// One workgroup per problem of t, all with small or all with big planes.
+void launch_tail_table(hipStream_t stream, int dtype, bool kv, bool big, const TableLaunch& t);
 
 // ---- status (kernels_basic.hip); descriptors are StatusDesc ------------------------------
 void launch_batch_init(hipStream_t stream, const TableLaunch& t);  // act = 1, cyc = 0

@@ -142,7 +142,7 @@ __device__ __forceinline__ T wtot(const T* w)
     return S;
 }
 
-__device__ __forceinline__ int diag_count(int bc, int dim, int nout)
+__host__ __device__ __forceinline__ int diag_count(int bc, int dim, int nout)
 {
     return (2 * dim - nout) + (bc == BC_DIRICHLET ? 2 * nout : 0);
 }
