@@ -235,8 +235,16 @@ __device__ __forceinline__ void tile_pass(const TileArgs<T>& a, int b, int t, in
         if (w > 0) up = buf[(w - 1) * 128 + 64 + lane];
         if (w < WV - 1) dn = buf[(w + 1) * 128 + lane];
     };
-    // Cell kappa: the kappa rows above and below the band, read once.
-    V kup, kdn;
+    // Cell kappa is bound by its divisions (a correctly rounded FP64 division is about a dozen
+    // instructions) and by the registers that decide how many blocks share a compute unit.
+    // With four face weights formed at each use a wave made 92 divisions in 158 VGPRs, one
+    // block per compute unit, and the passes at 2048^2 took 91 (pre) and 97 us (post with the
+    // norm); forming each face once leaves 34 divisions in 128 VGPRs, two blocks, and 50.9 and
+    // 44.6 us.  (Weights read from tables in memory would move 41 bytes per cell and pass
+    // instead of 33: about the time of the 18 divisions they save.)
+    // Cell kappa: the band edges' kappa rows (read once, after exchange 0), and the face
+    // weights of the band, each formed once: wl / wi / wr left of, inside and right of the
+    // pair of a row, wye / wyo below row r (r == B: above the band) in the even / odd column.
     if constexpr (KV) {
         V top, bot;
         top.x = ke[0];
@@ -246,32 +254,20 @@ __device__ __forceinline__ void tile_pass(const TileArgs<T>& a, int b, int t, in
         kxch[w * 128 + lane] = top;
         kxch[w * 128 + 64 + lane] = bot;
     }
-    // Cell kappa: weighted neighbour sum Sw and weight total Wt of the even (EVEN) or odd
-    // cell of row r, with the face weights and boundary faces of fas_device.h's gather
-    // (slot order x-, x+, y-, y+; a boundary face weighs kdir * kappa_p).
+    T wl[KV ? B : 1], wi[KV ? B : 1], wr[KV ? B : 1], wye[KV ? B + 1 : 1], wyo[KV ? B + 1 : 1];
+    // Weighted neighbour sum Sw and weight total Wt of the even (EVEN) or odd cell of row r
+    // (slot order x-, x+, y-, y+, as fas_device.h's gather).
     auto kv_terms = [&](bool even, int r, T& Sw, T& Wt) {
         if (even) {
-            const T kp = ke[r], uw = dpp_move<kShr1>(uo[r]), kw = dpp_move<kShr1>(ko[r]);
+            const T uw = dpp_move<kShr1>(uo[r]);
             const T uem = r > 0 ? ue[r - 1] : up.x, uep = r < B - 1 ? ue[r + 1] : dn.x;
-            const T kem = r > 0 ? ke[r - 1] : kup.x, kep = r < B - 1 ? ke[r + 1] : kdn.x;
-            const T wb = kdir * kp;
-            const T w0 = bxe ? wb : face_w(kw, kp);
-            const T w1 = face_w(kp, ko[r]);
-            const T w2 = ys[r] ? wb : face_w(kem, kp);
-            const T w3 = yn[r] ? wb : face_w(kp, kep);
-            Sw = (w0 * uw + w1 * uo[r]) + (w2 * uem + w3 * uep);
-            Wt = (w0 + w1) + (w2 + w3);
+            Sw = (wl[r] * uw + wi[r] * uo[r]) + (wye[r] * uem + wye[r + 1] * uep);
+            Wt = (wl[r] + wi[r]) + (wye[r] + wye[r + 1]);
         } else {
-            const T kp = ko[r], uE = dpp_move<kShl1>(ue[r]), kE = dpp_move<kShl1>(ke[r]);
+            const T uE = dpp_move<kShl1>(ue[r]);
             const T uom = r > 0 ? uo[r - 1] : up.y, uop = r < B - 1 ? uo[r + 1] : dn.y;
-            const T kom = r > 0 ? ko[r - 1] : kup.y, kop = r < B - 1 ? ko[r + 1] : kdn.y;
-            const T wb = kdir * kp;
-            const T w0 = face_w(ke[r], kp);
-            const T w1 = bxo ? wb : face_w(kp, kE);
-            const T w2 = ys[r] ? wb : face_w(kom, kp);
-            const T w3 = yn[r] ? wb : face_w(kp, kop);
-            Sw = (w0 * ue[r] + w1 * uE) + (w2 * uom + w3 * uop);
-            Wt = (w0 + w1) + (w2 + w3);
+            Sw = (wi[r] * ue[r] + wr[r] * uE) + (wyo[r] * uom + wyo[r + 1] * uop);
+            Wt = (wi[r] + wr[r]) + (wyo[r] + wyo[r + 1]);
         }
     };
     // Neighbour sums and diagonal counts (weighted, with cell kappa) of both cells of
@@ -294,11 +290,33 @@ __device__ __forceinline__ void tile_pass(const TileArgs<T>& a, int b, int t, in
 
     exchange(0);  // its barrier also publishes the kappa edges
     if constexpr (KV) {
+        V kup, kdn;
         kup.x = (T)0;
         kup.y = (T)0;
         kdn = kup;
         if (w > 0) kup = kxch[(w - 1) * 128 + 64 + lane];
         if (w < WV - 1) kdn = kxch[(w + 1) * 128 + lane];
+        // the weights of fas_device.h's gather: harmonic means, kdir * kappa_p on a boundary
+        // face.  A face shared by two lanes is formed by the left one and shifted; one shared
+        // with a row outside the domain has the inside row's boundary weight.
+#pragma unroll
+        for (int r = 0; r < B; ++r) {
+            wi[r] = face_w(ke[r], ko[r]);
+            wr[r] = face_w(ko[r], dpp_move<kShl1>(ke[r]));
+            if (XE) wr[r] = bxo ? kdir * ko[r] : wr[r];
+            wl[r] = dpp_move<kShr1>(wr[r]);
+            if (XE) wl[r] = bxe ? kdir * ke[r] : wl[r];
+        }
+#pragma unroll
+        for (int r = 0; r <= B; ++r) {
+            const T em = r > 0 ? ke[r - 1] : kup.x, ep = r < B ? ke[r] : kdn.x;
+            const T om = r > 0 ? ko[r - 1] : kup.y, op = r < B ? ko[r] : kdn.y;
+            T we = face_w(em, ep), wo = face_w(om, op);
+            if (r > 0 && yn[r - 1]) we = kdir * em, wo = kdir * om;
+            if (r < B && ys[r]) we = kdir * ep, wo = kdir * op;
+            wye[r] = we;
+            wyo[r] = wo;
+        }
     }
     if constexpr (RHS) {
         // FAS right-hand side from the initial values: f = r + A u
@@ -406,8 +424,10 @@ __device__ __forceinline__ void tile_pass(const TileArgs<T>& a, int b, int t, in
     }
 }
 
+// (Cell kappa: four waves per SIMD, 128 VGPRs, so that two 8-wave blocks share a compute unit;
+// the FP64 edge variants spill five registers for it.)
 template <typename T, int NU, int MODE, bool NORM, int IN, bool KV, int FIRST>
-__global__ __launch_bounds__(64 * (KV ? kMaxTileWavesKV : kMaxTileWaves)) void k_tile(TileArgs<T> a)
+__global__ __launch_bounds__(64 * (KV ? kMaxTileWavesKV : kMaxTileWaves), KV ? 4 : 1) void k_tile(TileArgs<T> a)
 {
     // neighbouring tiles, which share halo cells, run on one XCD
     const int blk = (int)xcd_block(blockIdx.x, gridDim.x);
@@ -429,7 +449,7 @@ __global__ __launch_bounds__(64 * (KV ? kMaxTileWavesKV : kMaxTileWaves)) void k
 // FAS right-hand side, one with partials sums f^2 per tile; a post-pass descriptor with
 // partials sums the residual's squares per tile.
 template <typename T, int NU, bool POSTP, bool KV, int FIRST>
-__global__ __launch_bounds__(64 * (KV ? kMaxTileWavesKV : kMaxTileWaves)) void k_tile_table(TableLaunch tl)
+__global__ __launch_bounds__(64 * (KV ? kMaxTileWavesKV : kMaxTileWaves), KV ? 4 : 1) void k_tile_table(TableLaunch tl)
 {
     const int blk = (int)xcd_block(blockIdx.x, gridDim.x);
     int lo = 0, hi = tl.np - 1;  // the problem p with first[p] <= blk < first[p + 1]
