@@ -14,6 +14,7 @@
 
 #include "fas_device.h"
 #include "fas_internal.h"
+#include "march_util.h"
 #include "stag_internal.h"
 
 namespace fas {
@@ -165,103 +166,104 @@ __global__ __launch_bounds__(256) void k_correct(Lev Lf, Coarse C, const double*
     udst[t] = usrc[t] + prolong_point<LOC>(C, (int)(t % Lf.nx), (int)(t / Lf.nx));
 }
 
-// Coarse corrections a lane's window columns need, loaded at once: e(K', J') for K' in
-// {K} (cells), {K-1, K} (EW edges) or {K-1, K, K+1} (NS edges), K = x0 / 2, and the RPW/2 + 3
-// coarse rows around the lane's rows.  pe<PAR, I, S>() evaluates prolong_point at
-// (x0 + S, yw + I) from the table with the same operations (yw of parity PAR), so the result
-// is the same bit for bit; entries outside the coarse grid are never used.
+// The FAS corrections of a lane's window columns (x0, x0 + 1) and rows yw .. yw + RPW - 1.  A
+// lane loads e(K, J) for its own coarse column K = x0 / 2 and the RPW/2 + 3 coarse rows
+// around its rows, and takes what the neighbouring columns give from the neighbouring lanes
+// (the window's first even and last odd column come out wrong: one column of margin).
+// add<PAR, I>() corrects row yw + I (yw of parity PAR) with the operations of prolong_point,
+// so the result is the same bit for bit; entries outside the coarse grid are never used.
 template <int LOC, int RPW>
 struct CorrTable {
-    static constexpr int NK = LOC == LOC_CELL ? 1 : (LOC == LOC_EDGE_X ? 2 : 3);
     static constexpr int NJ = RPW / 2 + 3;
-    double E[NK][NJ];
+    double E[NJ];
     int K, Jb;
     __device__ __forceinline__ void load(const Coarse& C, int x0, int yw)
     {
         K = x0 >> 1;
         Jb = (yw >> 1) - 1;
-        const int Kb = K - (LOC == LOC_CELL ? 0 : 1);
+        double c0[NJ];
+        const int Kl = min(max(K, 0), C.ncx - 1);
 #pragma unroll
-        for (int kk = 0; kk < NK; ++kk)
+        for (int jj = 0; jj < NJ; ++jj) {
+            const size_t i = (size_t)min(max(Jb + jj, 0), C.ncy - 1) * C.ncx + Kl;
+            E[jj] = C.uc[i];
+            c0[jj] = C.uc0[i];
+        }
 #pragma unroll
-            for (int jj = 0; jj < NJ; ++jj) {
-                const int Kq = Kb + kk, Jq = Jb + jj;
-                E[kk][jj] = (Kq >= 0 && Kq < C.ncx && Jq >= 0 && Jq < C.ncy) ? C.e(Kq, Jq) : 0.0;
-            }
+        for (int jj = 0; jj < NJ; ++jj) E[jj] = E[jj] - c0[jj];
     }
-    template <int PAR, int I, int S>
-    __device__ __forceinline__ double pe(const Coarse& C) const
+    template <int PAR, int I>
+    __device__ __forceinline__ void add(const Coarse& C, bool in0, bool in1, double& u0, double& u1) const
     {
         constexpr int jj = ((PAR + I) >> 1) + 1;  // J - Jb
         constexpr bool yodd = ((PAR + I) & 1) != 0;
         const int J = Jb + jj;
+        double p0, p1;
         if constexpr (LOC == LOC_CELL) {
-            return E[0][jj];
+            p0 = p1 = E[jj];
         } else if constexpr (LOC == LOC_EDGE_X) {
-            auto col = [&](int kk) {
-                const double e0 = E[kk][jj];
-                const double nb = yodd ? (J < C.ncy - 1 ? E[kk][jj + 1] : -e0) : (J > 0 ? E[kk][jj - 1] : -e0);
-                return lin_cell(e0, nb);
-            };
-            if constexpr (S == 1) {
-                return col(1);
-            } else {
-                const double left = K >= 1 ? col(0) : 0.0;
-                const double right = K <= C.ncx - 1 ? col(1) : 0.0;
-                return (left + right) * 0.5;
-            }
+            // linear along y in column K; the even point takes the mean with column K - 1
+            const double e0 = E[jj];
+            const double nb = yodd ? (J < C.ncy - 1 ? E[jj + 1] : -e0) : (J > 0 ? E[jj - 1] : -e0);
+            p1 = lin_cell(e0, nb);
+            const double l = dpp_move<kShr1>(p1);
+            const double left = K >= 1 ? l : 0.0, right = K <= C.ncx - 1 ? p1 : 0.0;
+            p0 = (left + right) * 0.5;
         } else {
-            auto row = [&](int j) {
-                const double e0 = E[1][j];
-                const double nb = S == 1 ? (K < C.ncx - 1 ? E[2][j] : -e0) : (K > 0 ? E[0][j] : -e0);
-                return lin_cell(e0, nb);
+            // linear along x in coarse row j; an even row takes the mean of rows J - 1 and J
+            auto row = [&](int j, double& r0, double& r1) {
+                const double e0 = E[j], l = dpp_move<kShr1>(E[j]), r = dpp_move<kShl1>(E[j]);
+                r0 = lin_cell(e0, K > 0 ? l : -e0);
+                r1 = lin_cell(e0, K < C.ncx - 1 ? r : -e0);
             };
             if constexpr (yodd) {
-                return row(jj);
+                row(jj, p0, p1);
             } else {
-                const double below = J >= 1 ? row(jj - 1) : 0.0;
-                const double above = J <= C.ncy - 1 ? row(jj) : 0.0;
-                return (below + above) * 0.5;
+                double b0, b1, a0, a1;
+                row(jj - 1, b0, b1);
+                row(jj, a0, a1);
+                const bool below = J >= 1, above = J <= C.ncy - 1;
+                p0 = ((below ? b0 : 0.0) + (above ? a0 : 0.0)) * 0.5;
+                p1 = ((below ? b1 : 0.0) + (above ? a1 : 0.0)) * 0.5;
             }
         }
+        u0 = in0 ? u0 + p0 : u0;
+        u1 = in1 ? u1 + p1 : u1;
     }
 };
-
-template <int LOC, int RPW, int PAR, int I>
-__device__ __forceinline__ void corr_row(const CorrTable<LOC, RPW>& T, const Coarse& C, int yw, int ny, bool in0,
-                                         bool in1, double (&u0)[RPW], double (&u1)[RPW])
-{
-    const int gy = yw + I;
-    if (gy < 0 || gy >= ny) return;
-    if (in0) u0[I] = u0[I] + T.template pe<PAR, I, 0>(C);
-    if (in1) u1[I] = u1[I] + T.template pe<PAR, I, 1>(C);
-}
 
 template <int LOC, int RPW, int PAR, int... I>
 __device__ __forceinline__ void corr_rows(const CorrTable<LOC, RPW>& T, const Coarse& C, int yw, int ny, bool in0,
                                           bool in1, double (&u0)[RPW], double (&u1)[RPW],
                                           std::integer_sequence<int, I...>)
 {
-    (corr_row<LOC, RPW, PAR, I>(T, C, yw, ny, in0, in1, u0, u1), ...);
+    ((yw + I >= 0 && yw + I < ny ? T.template add<PAR, I>(C, in0, in1, u0[I], u1[I]) : (void)0), ...);
 }
 
-// ---- red-black sweeps on an LDS window ------------------------------------------------------
-// A 512-thread block (8 waves) loads a 128-column window of the iterate into LDS: lane l of a
-// wave owns the column pair (2l, 2l + 1) of the window and each wave WY/8 rows, whose
-// right-hand side values stay in registers.  The block runs nu red-black sweeps on the window
-// and writes its interior.  Half-sweep k updates values at distance >= k from the window's
-// edge correctly, so after 2 nu half-sweeps the values at distance >= 2 nu are exactly what
-// nu sweeps over the whole grid give.  Values outside the grid stay 0 in LDS (the 0.0
-// neighbours of the point formula).  Within a half-sweep the updated points read only
-// points of the other colour, so the update runs in place.  Window geometry (rows, margins of
-// the written region): sweep_geom().  Windows are 32 rows: 54 to 105 VGPRs and 32 KiB of
-// LDS, so two to four blocks share a compute unit (64-row windows, with half the halo share,
-// measured slower in every variant).
+// ---- red-black sweeps on a window held in registers -----------------------------------------
+// A 512-thread block (8 waves) loads a 128-column window of the iterate and right-hand side:
+// lane l of a wave owns the column pair (2l, 2l + 1) of the window and each wave WY/8 rows, all
+// in registers.  x-neighbours come from the adjacent lane by DPP; before each half-sweep the
+// waves trade the first and last row of their bands through LDS (double-buffered: one barrier
+// per half-sweep).  Half-sweep k updates values at distance >= k from the window's edge
+// correctly, so after 2 nu half-sweeps the values at distance >= 2 nu are exactly what nu
+// sweeps over the whole grid give.  Values outside the grid stay 0 (the 0.0 neighbours of the
+// point formula).  Window geometry (rows, margins of the written region): sweep_geom(); the
+// window origin is an even column and a row of fixed parity, so the column of a pair that a
+// half-sweep updates is known at compile time, row by row.
 //
-// The window origin is even (the margins and the interior width are even along x), so in a
-// row of one colour exactly one column of every pair is updated, the same one for the whole
-// wave: every lane updates one point per row.  Even and odd columns sit in separate LDS
-// arrays, which makes every LDS access of a wave 64 consecutive doubles.
+// What bounds it: memory on the large levels (an edge row is odd, so rows start at any 8-byte
+// boundary; a pair is one 16-byte access all the same), the chain of half-sweeps on the small
+// ones.  The form that kept the window in LDS (two planes, every neighbour an LDS read) was
+// bound by its LDS accesses: at 4096^2, two sweeps with the restriction took 124-132 us, with
+// correction and norm 126 (cells), 142 (EW) and 177 us (NS edges); now 96-107 and 116-123 us
+// (4.4-5 TB/s), and 7-8 instead of 9 us on small levels.  Eight waves, two blocks per compute
+// unit: blocks of 5 and 10 waves took 134-175 us (they fill the SIMDs unevenly), and 80 VGPRs
+// for a third block spill.  Divisions by a precomputed reciprocal and two corrections (the
+// same bits) gained 1.5% and were not worth their range checks.
+//
+// XE: the window reaches past a domain x-edge; the other windows need no column masks and
+// have one diagonal.
 //
 // Variants (each a fixed set of point formulas of the per-level kernels, so the results are
 // the same bit for bit):
@@ -271,111 +273,127 @@ __device__ __forceinline__ void corr_rows(const CorrTable<LOC, RPW>& T, const Co
 //   RHS   f holds the restricted residual r of the finer level: the FAS right-hand side
 //         f = r + L u is formed from the loaded window before the sweeps (as k_coarse_rhs)
 //         and written to io.fout;
-//   RES   after the sweeps, the residual is formed in registers and the block restricts its
-//         written region into the coarse level (as k_restrict): io.uc = io.uc0 = R u,
-//         io.rc = R r.  Along an edge axis the third tap of a coarse point lies one column
-//         (lane shuffle) or one row (exchanged through LDS across waves) past the region.
-template <int NU, int LOC, bool CORR, bool NORM, bool RHS, bool RES>
-__global__ __launch_bounds__(512) void k_sweep(Lev L, const double* __restrict__ f, const double* __restrict__ uin,
-                                               double* __restrict__ uout, int tiles_x, SweepIO io)
+//   RES   after the sweeps, the residual is formed and the block restricts its written region
+//         into the coarse level (as k_restrict): io.uc0 = R u, io.rc = R r.  Along an edge axis
+//         the third tap of a coarse point lies one column (the next lane) or one row (the next
+//         wave's first, traded through LDS) past the region.
+typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));  // a pair at any 8-byte boundary
+
+struct SweepShared {
+    double2 xch[2][kSweepWaves][2][kTile];  // two buffers of each wave's first and last row
+    double red[kSweepWaves];      // wave sums of the norm
+};
+
+// The entry of a PointCoef table for a point at an x wall (bx) and / or a y wall (by).
+__device__ __forceinline__ double by_wall(bool bx, bool by, double v0, double v1, double v2, double v3)
 {
-    constexpr SweepGeom G = sweep_geom(NU, NORM, RES);
-    constexpr int WY = G.wy, HX = G.hx, HY = G.hy, OX = G.ox, OY = G.oy, RPW = WY / 8;
-    static_assert(HX % 2 == 0 && OY % 2 == 0 && RPW % 2 == 0, "window geometry");
-    __shared__ double se[WY][kTile];  // even columns of the window
-    __shared__ double so[WY][kTile];  // odd columns
-    const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int tx = (int)(b % (unsigned)tiles_x), ty = (int)(b / (unsigned)tiles_x);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const double a = by ? v2 : v0, b = by ? v3 : v1;
+    return bx ? b : a;
+}
+
+template <int NU, int LOC, bool CORR, bool NORM, bool RHS, bool RES, bool XE>
+__device__ __forceinline__ void sweep_pass(const Lev& L, const PointCoef& P, const double* __restrict__ f,
+                                           const double* __restrict__ uin, double* __restrict__ uout, int tx, int ty,
+                                           const SweepIO& io, SweepShared& sh)
+{
+    constexpr SweepGeom G = sweep_geom(NU, CORR, NORM, RES);
+    constexpr int WV = kSweepWaves, RPW = G.wy / WV, HX = G.hx, HY = G.hy, OX = G.ox, OY = G.oy;
+    static_assert(HX % 2 == 0 && OX % 2 == 0 && OY % 2 == 0 && RPW % 2 == 0, "window geometry");
+    static_assert(!RES || HY % 2 == 0, "2 x 2 blocks of the restriction");
+    auto& xch = sh.xch;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int x0 = tx * OX - HX + 2 * lane;  // grid column of the lane's even column
-    const int yw = ty * OY - HY + w * RPW;   // grid row of the wave's first row
-    const bool in0 = x0 >= 0 && x0 < L.nx, in1 = x0 + 1 >= 0 && x0 + 1 < L.nx;
+    const int yw = ty * OY - HY + w * RPW;   // grid row of the wave's first row (parity of HY)
+    const bool in0 = !XE || (x0 >= 0 && x0 < L.nx), in1 = !XE || (x0 + 1 >= 0 && x0 + 1 < L.nx);
     double u0[RPW], u1[RPW], f0[RPW], f1[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
         const int gy = yw + i;
         const bool row = gy >= 0 && gy < L.ny;
-        const size_t idx = row ? (size_t)gy * L.nx + (size_t)(in0 ? x0 : 0) : 0;
-        u0[i] = row && in0 ? uin[idx] : 0.0;
-        f0[i] = row && in0 ? f[idx] : 0.0;
-        u1[i] = row && in1 ? uin[(size_t)gy * L.nx + x0 + 1] : 0.0;
-        f1[i] = row && in1 ? f[(size_t)gy * L.nx + x0 + 1] : 0.0;
+        const size_t idx = (size_t)min(max(gy, 0), L.ny - 1) * L.nx;
+        if constexpr (!XE) {
+            const pair_t vu = *reinterpret_cast<const pair_t*>(uin + idx + x0);
+            const pair_t vf = *reinterpret_cast<const pair_t*>(f + idx + x0);
+            u0[i] = row ? vu.x : 0.0;
+            u1[i] = row ? vu.y : 0.0;
+            f0[i] = row ? vf.x : 0.0;
+            f1[i] = row ? vf.y : 0.0;
+        } else {
+            const size_t a = idx + (in0 ? x0 : 0), b = idx + (in1 ? x0 + 1 : 0);
+            const double v0 = uin[a], v1 = uin[b], g0 = f[a], g1 = f[b];
+            u0[i] = row && in0 ? v0 : 0.0;
+            u1[i] = row && in1 ? v1 : 0.0;
+            f0[i] = row && in0 ? g0 : 0.0;
+            f1[i] = row && in1 ? g1 : 0.0;
+        }
     }
-    if (CORR) {
+    if constexpr (CORR) {
         // the coarse values are loaded with the window, then P e is added row by row
         CorrTable<LOC, RPW> T;
         T.load(io.C, x0, yw);
-        if (yw & 1)
-            corr_rows<LOC, RPW, 1>(T, io.C, yw, L.ny, in0, in1, u0, u1, std::make_integer_sequence<int, RPW>{});
-        else
-            corr_rows<LOC, RPW, 0>(T, io.C, yw, L.ny, in0, in1, u0, u1, std::make_integer_sequence<int, RPW>{});
+        corr_rows<LOC, RPW, HY & 1>(T, io.C, yw, L.ny, in0, in1, u0, u1, std::make_integer_sequence<int, RPW>{});
     }
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        se[w * RPW + i][lane] = u0[i];
-        so[w * RPW + i][lane] = u1[i];
-    }
-    // k along x of the two columns
-    double kx0 = 4.0, kx1 = 4.0;
-    if (x0 == 0) kx0 += kshift(L.kx);
-    if (x0 == L.nx - 1) kx0 += kshift(L.kx);
-    if (x0 + 1 == 0) kx1 += kshift(L.kx);
-    if (x0 + 1 == L.nx - 1) kx1 += kshift(L.kx);
-    auto kyof = [&](int gy) {
-        double ky = 0.0;
-        if (gy == 0) ky += kshift(L.ky);
-        if (gy == L.ny - 1) ky += kshift(L.ky);
-        return ky;
+    // walls: of the two columns along x, of a row along y
+    const bool bx0 = XE && (x0 == 0 || x0 == L.nx - 1), bx1 = XE && (x0 + 1 == 0 || x0 + 1 == L.nx - 1);
+    const double D0 = P.D[0], D1 = P.D[1], D2 = P.D[2], D3 = P.D[3];
+    const int ny = L.ny;
+    auto D_at = [=](bool bx, int i) { return by_wall(XE && bx, yw + i == 0 || yw + i == ny - 1, D0, D1, D2, D3); };
+    // The row above the wave's band (the next wave's first) and below it (the previous wave's
+    // last), as they stand after the last half-sweep.  Exchange e writes buffer e & 1: a wave
+    // can only overwrite a buffer after the next barrier, which every wave passes only once
+    // it has read that buffer.
+    double2 dn, up;
+    auto exchange = [&](int e) {
+        xch[e & 1][w][0][lane] = double2{u0[0], u1[0]};
+        xch[e & 1][w][1][lane] = double2{u0[RPW - 1], u1[RPW - 1]};
+        __syncthreads();
+        dn = double2{0.0, 0.0};
+        up = dn;
+        if (w > 0) dn = xch[e & 1][w - 1][1][lane];
+        if (w < WV - 1) up = xch[e & 1][w + 1][0][lane];
     };
-    // L u at the even / odd point of window row r from the values in LDS
-    auto Lu_even = [&](int r, double ky) {
-        const double D = L.a * L.h2 + L.c * (kx0 + ky);
-        const double s = (so[r][lane - 1] + so[r][lane]) + (se[r - 1][lane] + se[r + 1][lane]);
-        return (D * se[r][lane] - L.c * s) * L.ih2;
+    // neighbour sums of the even / odd point of row i
+    auto sum_even = [&](int i) {
+        const double S = i > 0 ? u0[i - 1] : dn.x, N = i < RPW - 1 ? u0[i + 1] : up.x;
+        return (dpp_move<kShr1>(u1[i]) + u1[i]) + (S + N);
     };
-    auto Lu_odd = [&](int r, double ky) {
-        const double D = L.a * L.h2 + L.c * (kx1 + ky);
-        const double s = (se[r][lane] + se[r][lane + 1]) + (so[r - 1][lane] + so[r + 1][lane]);
-        return (D * so[r][lane] - L.c * s) * L.ih2;
+    auto sum_odd = [&](int i) {
+        const double S = i > 0 ? u1[i - 1] : dn.y, N = i < RPW - 1 ? u1[i + 1] : up.y;
+        return (u0[i] + dpp_move<kShl1>(u0[i])) + (S + N);
     };
-    __syncthreads();
-    if (RHS) {
-        // f = r + L u from the values as loaded, at every point with its four neighbours in
-        // the window (the sweeps update no other)
+    auto Lu_even = [&](int i) { return (D_at(bx0, i) * u0[i] - L.c * sum_even(i)) * L.ih2; };
+    auto Lu_odd = [&](int i) { return (D_at(bx1, i) * u1[i] - L.c * sum_odd(i)) * L.ih2; };
+    exchange(0);
+    if constexpr (RHS) {
+        // f = r + L u from the values as loaded
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
-            const int r = w * RPW + i, gy = yw + i;
-            if (r < 1 || r > WY - 2 || gy < 0 || gy >= L.ny) continue;
-            const double ky = kyof(gy);
-            if (in0 && lane >= 1) f0[i] = f0[i] + Lu_even(r, ky);
-            if (in1 && lane <= 62) f1[i] = f1[i] + Lu_odd(r, ky);
+            f0[i] = f0[i] + Lu_even(i);
+            f1[i] = f1[i] + Lu_odd(i);
         }
-        __syncthreads();
     }
 #pragma unroll
     for (int hs = 0; hs < 2 * NU; ++hs) {
+        if (hs > 0) exchange(hs);
         const int colour = (hs & 1) ^ 1;  // sets 1-2 (odd index sum) first
+        double q[RPW];
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
-            const int r = w * RPW + i, gy = yw + i;
-            if (r < 1 || r > WY - 2 || gy < 0 || gy >= L.ny) continue;
-            const int odd = (colour + gy) & 1;  // the pair's column with this colour (wave-uniform)
-            double k = odd ? kx1 : kx0;
-            if (gy == 0) k += kshift(L.ky);
-            if (gy == L.ny - 1) k += kshift(L.ky);
-            const double D = L.a * L.h2 + L.c * k;
-            if (odd) {
-                if (lane == 63 || !in1) continue;
-                const double s = (se[r][lane] + se[r][lane + 1]) + (so[r - 1][lane] + so[r + 1][lane]);
-                so[r][lane] = (L.c * s + L.h2 * f1[i]) / D;
-            } else {
-                if (lane == 0 || !in0) continue;
-                const double s = (so[r][lane - 1] + so[r][lane]) + (se[r - 1][lane] + se[r + 1][lane]);
-                se[r][lane] = (L.c * s + L.h2 * f0[i]) / D;
-            }
+            const bool odd = (colour + HY + i) & 1;  // the pair's column with this colour
+            q[i] = (L.c * (odd ? sum_odd(i) : sum_even(i)) + L.h2 * (odd ? f1[i] : f0[i])) / D_at(odd ? bx1 : bx0, i);
         }
-        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            const bool odd = (colour + HY + i) & 1;
+            const bool row = yw + i >= 0 && yw + i < L.ny;
+            if (odd)
+                u1[i] = row && in1 ? q[i] : u1[i];
+            else
+                u0[i] = row && in0 ? q[i] : u0[i];
+        }
     }
+    if constexpr (NORM || RES) exchange(2 * NU);
     const bool colw = 2 * lane >= HX && 2 * lane < HX + OX;  // the lane's pair is written
     double acc = 0.0;
     if (colw) {
@@ -383,60 +401,66 @@ __global__ __launch_bounds__(512) void k_sweep(Lev L, const double* __restrict__
         for (int i = 0; i < RPW; ++i) {
             const int r = w * RPW + i, gy = yw + i;
             if (r < HY || r >= HY + OY || gy < 0 || gy >= L.ny) continue;
-            if (in0) uout[(size_t)gy * L.nx + x0] = se[r][lane];
-            if (in1) uout[(size_t)gy * L.nx + x0 + 1] = so[r][lane];
-            if (RHS) {
-                if (in0) io.fout[(size_t)gy * L.nx + x0] = f0[i];
-                if (in1) io.fout[(size_t)gy * L.nx + x0 + 1] = f1[i];
-            }
-            if (NORM) {
-                const double ky = kyof(gy);
-                if (in0) {
-                    const double rv = f0[i] - Lu_even(r, ky);
-                    acc = acc + rv * rv;
-                }
-                if (in1) {
-                    const double rv = f1[i] - Lu_odd(r, ky);
-                    acc = acc + rv * rv;
+            const size_t o = (size_t)gy * L.nx + x0;
+            if constexpr (!XE) {
+                *reinterpret_cast<pair_t*>(uout + o) = pair_t{u0[i], u1[i]};
+                if constexpr (RHS) *reinterpret_cast<pair_t*>(io.fout + o) = pair_t{f0[i], f1[i]};
+            } else {
+                if (in0) uout[o] = u0[i];
+                if (in1) uout[o + 1] = u1[i];
+                if constexpr (RHS) {
+                    if (in0) io.fout[o] = f0[i];
+                    if (in1) io.fout[o + 1] = f1[i];
                 }
             }
         }
     }
-    if (NORM) {
-        // fixed-order reduction: butterfly within each wave, then the 8 wave sums in order
+    if constexpr (NORM || RES) {
+        // residuals f - L u in place of f (right wherever every neighbour is final: the written
+        // region and, with RES, one ring around it)
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            f0[i] = f0[i] - Lu_even(i);
+            f1[i] = f1[i] - Lu_odd(i);
+        }
+    }
+    if constexpr (NORM) {
+        if (colw) {
+#pragma unroll
+            for (int i = 0; i < RPW; ++i) {
+                const int r = w * RPW + i, gy = yw + i;
+                if (r < HY || r >= HY + OY || gy < 0 || gy >= L.ny) continue;
+                if (in0) acc = acc + f0[i] * f0[i];
+                if (in1) acc = acc + f1[i] * f1[i];
+            }
+        }
+        // fixed-order reduction: butterfly within each wave, then the wave sums in order
         for (int o = 32; o > 0; o >>= 1) acc = acc + __shfl_xor(acc, o, 64);
-        __shared__ double red[8];
-        if (lane == 0) red[w] = acc;
+        if (lane == 0) sh.red[w] = acc;
         __syncthreads();
         if (threadIdx.x == 0) {
-            double t = red[0];
-            for (int k = 1; k < 8; ++k) t = t + red[k];
+            double t = sh.red[0];
+            for (int k = 1; k < WV; ++k) t = t + sh.red[k];
             io.partials[blockIdx.x] = t;
         }
     }
-    if (RES) {
-        // residuals f - L u in place of f, wherever every neighbour is final (distance
-        // >= 2 nu + 1 from the window edge; the written region and one ring around it)
-#pragma unroll
-        for (int i = 0; i < RPW; ++i) {
-            const int r = w * RPW + i, gy = yw + i;
-            if (r < 2 * NU + 1 || r > WY - 2 * NU - 2 || gy < 0 || gy >= L.ny) continue;
-            const double ky = kyof(gy);
-            if (in0 && 2 * lane >= 2 * NU + 1) f0[i] = f0[i] - Lu_even(r, ky);
-            if (in1 && 2 * lane + 1 <= 2 * kTile - 2 * NU - 2) f1[i] = f1[i] - Lu_odd(r, ky);
-        }
+    if constexpr (RES) {
         // the third tap of an edge axis: the next lane's even column (EDGE_X), the next
-        // wave's first row (EDGE_Y)
-        double nx0[RPW];
-        if (LOC == LOC_EDGE_X) {
+        // wave's first row (EDGE_Y; its values of u are the row above the band)
+        double nx0[RPW], nu0[RPW];
+        double2 rup = double2{0.0, 0.0};
+        if constexpr (LOC == LOC_EDGE_X) {
 #pragma unroll
-            for (int i = 0; i < RPW; ++i) nx0[i] = __shfl_down(f0[i], 1, 64);
+            for (int i = 0; i < RPW; ++i) {
+                nx0[i] = dpp_move<kShl1>(f0[i]);
+                nu0[i] = dpp_move<kShl1>(u0[i]);
+            }
         }
-        __shared__ double xre[LOC == LOC_EDGE_Y ? 8 : 1][kTile], xro[LOC == LOC_EDGE_Y ? 8 : 1][kTile];
-        if (LOC == LOC_EDGE_Y) {
-            xre[w][lane] = f0[0];
-            xro[w][lane] = f1[0];
+        if constexpr (LOC == LOC_EDGE_Y) {
+            constexpr int b = (2 * NU + 1) & 1;  // the buffer of the exchange before the last
+            xch[b][w][0][lane] = double2{f0[0], f1[0]};
             __syncthreads();
+            if (w < WV - 1) rup = xch[b][w + 1][0][lane];
         }
         if (colw) {
             const int K = x0 >> 1;  // x0 >= 0 here
@@ -448,32 +472,48 @@ __global__ __launch_bounds__(512) void k_sweep(Lev L, const double* __restrict__
                 if (J >= io.ncy || K >= io.ncx) continue;
                 double ru, rr;
                 if (LOC == LOC_CELL) {
-                    ru = ((se[r][lane] + so[r][lane]) + (se[r + 1][lane] + so[r + 1][lane])) * 0.25;
+                    ru = ((u0[2 * p] + u1[2 * p]) + (u0[2 * p + 1] + u1[2 * p + 1])) * 0.25;
                     rr = ((f0[2 * p] + f1[2 * p]) + (f0[2 * p + 1] + f1[2 * p + 1])) * 0.25;
                 } else if (LOC == LOC_EDGE_X) {
-                    const double gu0 = (se[r][lane] + 2.0 * so[r][lane]) + se[r][lane + 1];
-                    const double gu1 = (se[r + 1][lane] + 2.0 * so[r + 1][lane]) + se[r + 1][lane + 1];
+                    const double gu0 = (u0[2 * p] + 2.0 * u1[2 * p]) + nu0[2 * p];
+                    const double gu1 = (u0[2 * p + 1] + 2.0 * u1[2 * p + 1]) + nu0[2 * p + 1];
                     const double gr0 = (f0[2 * p] + 2.0 * f1[2 * p]) + nx0[2 * p];
                     const double gr1 = (f0[2 * p + 1] + 2.0 * f1[2 * p + 1]) + nx0[2 * p + 1];
                     ru = (gu0 + gu1) * 0.125;
                     rr = (gr0 + gr1) * 0.125;
                 } else {
-                    const double e2 = 2 * p + 2 < RPW ? f0[(2 * p + 2) % RPW] : xre[(w + 1) & 7][lane];
-                    const double o2 = 2 * p + 2 < RPW ? f1[(2 * p + 2) % RPW] : xro[(w + 1) & 7][lane];
-                    const double gu0 = (se[r][lane] + 2.0 * se[r + 1][lane]) + se[r + 2][lane];
-                    const double gu1 = (so[r][lane] + 2.0 * so[r + 1][lane]) + so[r + 2][lane];
+                    const bool last = 2 * p + 2 >= RPW;
+                    const double v0 = last ? up.x : u0[(2 * p + 2) % RPW], v1 = last ? up.y : u1[(2 * p + 2) % RPW];
+                    const double e2 = last ? rup.x : f0[(2 * p + 2) % RPW], o2 = last ? rup.y : f1[(2 * p + 2) % RPW];
+                    const double gu0 = (u0[2 * p] + 2.0 * u0[2 * p + 1]) + v0;
+                    const double gu1 = (u1[2 * p] + 2.0 * u1[2 * p + 1]) + v1;
                     const double gr0 = (f0[2 * p] + 2.0 * f0[2 * p + 1]) + e2;
                     const double gr1 = (f1[2 * p] + 2.0 * f1[2 * p + 1]) + o2;
                     ru = (gu0 + gu1) * 0.125;
                     rr = (gr0 + gr1) * 0.125;
                 }
                 const size_t c = (size_t)J * io.ncx + K;
-                io.uc[c] = ru;
                 io.uc0[c] = ru;
                 io.rc[c] = rr;
             }
         }
     }
+}
+
+template <int NU, int LOC, bool CORR, bool NORM, bool RHS, bool RES>
+__global__ __launch_bounds__(64 * kSweepWaves) void k_sweep(Lev L, PointCoef P, const double* __restrict__ f,
+                                               const double* __restrict__ uin, double* __restrict__ uout, int tiles_x,
+                                               SweepIO io)
+{
+    constexpr SweepGeom G = sweep_geom(NU, CORR, NORM, RES);
+    const unsigned b = xcd_block(blockIdx.x, gridDim.x);
+    const int tx = (int)(b % (unsigned)tiles_x), ty = (int)(b / (unsigned)tiles_x);
+    const int x0 = tx * G.ox - G.hx;
+    __shared__ SweepShared sh;
+    if (x0 <= 0 || x0 + 2 * kTile >= L.nx)
+        sweep_pass<NU, LOC, CORR, NORM, RHS, RES, true>(L, P, f, uin, uout, tx, ty, io, sh);
+    else
+        sweep_pass<NU, LOC, CORR, NORM, RHS, RES, false>(L, P, f, uin, uout, tx, ty, io, sh);
 }
 
 // ---- persistent coarse tail ------------------------------------------------------------------
@@ -508,7 +548,7 @@ __global__ __launch_bounds__(1024) void k_tail(TailArgs A)
     __shared__ double lds[kTailDoubles];
     const int n0 = A.op[0].nx * A.op[0].ny;
     for (int t = threadIdx.x; t < n0; t += blockDim.x) {
-        lds[A.ou[0] + t] = A.u[t];
+        lds[A.ou[0] + t] = A.uin[t];
         lds[A.of[0] + t] = A.r ? A.r[t] : A.f[t];
     }
     __syncthreads();
@@ -769,7 +809,8 @@ template <int NU, int LOC, bool CORR, bool NORM, bool RHS, bool RES>
 void sweep_go(hipStream_t s, dim3 grid, const Lev& L, const double* f, const double* uin, double* uout, int tx,
               const SweepIO& io)
 {
-    hipLaunchKernelGGL((k_sweep<NU, LOC, CORR, NORM, RHS, RES>), grid, dim3(512), 0, s, L, f, uin, uout, tx, io);
+    hipLaunchKernelGGL((k_sweep<NU, LOC, CORR, NORM, RHS, RES>), grid, dim3(64 * kSweepWaves), 0, s, L, point_coef(L), f, uin, uout,
+                       tx, io);
 }
 
 template <int NU, int LOC>
@@ -787,9 +828,20 @@ void sweep_flags(hipStream_t s, dim3 grid, const Lev& L, const double* f, const 
     }
 }
 
+PointCoef point_coef(const Lev& L)
+{
+    auto shift = [](int kind) { return kind == K_CN ? -1.0 : (kind == K_CD ? 1.0 : 0.0); };
+    PointCoef P;
+    for (int i = 0; i < 4; ++i) {
+        const double k = 4.0 + (i & 1 ? shift(L.kx) : 0.0) + (i & 2 ? shift(L.ky) : 0.0);
+        P.D[i] = L.a * L.h2 + L.c * k;
+    }
+    return P;
+}
+
 int sweep_blocks(const Lev& L, int nu, unsigned flags, int* tiles_x)
 {
-    const SweepGeom g = sweep_geom(nu, (flags & SW_NORM) != 0, (flags & SW_RES) != 0);
+    const SweepGeom g = sweep_geom(nu, (flags & SW_CORR) != 0, (flags & SW_NORM) != 0, (flags & SW_RES) != 0);
     const int tx = (L.nx + g.ox - 1) / g.ox, ty = (L.ny + g.oy - 1) / g.oy;
     if (tiles_x) *tiles_x = tx;
     return tx * ty;

@@ -210,16 +210,17 @@ double* sweeps(hipStream_t st, int loc, const Lev& L, const double* f, double* c
 
 int launches(int nu) { return nu / 2 + nu % 2; }
 
-// Pre-smoothing of the fused path: nu >= 1 sweeps from u (ut: the other buffer).  With r set,
-// the first launch forms the right-hand side f = r + L u (and writes f); the last restricts
-// the smoothed iterate and its residual into level C.  Returns the buffer holding the
-// smoothed iterate.
-double* pre_fused(hipStream_t st, int loc, const Lev& L, const double* r, double* f, double* u, double* ut, int nu,
-                  fas_stag::Level& C)
+// Pre-smoothing of the fused path: nu >= 1 sweeps from start, between the level's buffers u
+// and ut (start: one of them, or the level's u0, which is not written).  With r set, the
+// first launch forms the right-hand side f = r + L u (and writes f); the last restricts the
+// smoothed iterate and its residual into level C.  Returns the buffer holding the smoothed
+// iterate.
+double* pre_fused(hipStream_t st, int loc, const Lev& L, const double* r, double* f, const double* start, double* u,
+                  double* ut, int nu, fas_stag::Level& C)
 {
     const int twos = nu / 2, n = twos + nu % 2;
-    double* a = u;
-    double* b = ut;
+    const double* a = start;
+    double* b = start == ut ? u : ut;
     for (int i = 0; i < n; ++i) {
         SweepIO io{};
         unsigned flags = 0;
@@ -231,26 +232,28 @@ double* pre_fused(hipStream_t st, int loc, const Lev& L, const double* r, double
         }
         if (i == n - 1) {
             flags |= SW_RES;
-            io.uc = C.u;
             io.uc0 = C.u0;
             io.rc = C.r;
             io.ncx = C.nx;
             io.ncy = C.ny;
         }
         launch_sweep(st, loc, L, i < twos ? 2 : 1, fin, a, b, io, flags);
-        std::swap(a, b);
+        a = b;
+        b = b == ut ? u : ut;
     }
-    return a;
+    return const_cast<double*>(a);
 }
 
 // One V(nu1, nu2) cycle from level l on right-hand side f with the iterate in u (the result
 // returns to u).  r: the level's restricted residual when its right-hand side has yet to be
-// formed (f = r + L u; fused path, levels >= 1), else null.  Returns the number of residual
+// formed (f = r + L u; fused path, levels >= 1; the iterate is then in the level's u0, where
+// the finer level left R u), else null.  Returns the number of residual
 // partial sums the last sweep left in S.partials (0: none, the norm needs its own pass).
 int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1, int nu2, const double* r = nullptr)
 {
     const Lev L = level_op(S, l, a, c);
     double* ut = S.lev[l].ut;
+    const double* start = r ? S.lev[l].u0 : u;
     if (S.fused && l == S.tail_top) {
         TailArgs A{};
         A.nlev = S.L - l;
@@ -260,6 +263,7 @@ int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1
             A.of[k] = S.tail_of[k];
             A.ou0[k] = S.tail_ou0[k];
         }
+        A.uin = start;
         A.u = u;
         A.f = f;
         A.r = r;
@@ -270,7 +274,9 @@ int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1
         return 0;
     }
     if (r && (nu1 == 0 || l == S.L - 1)) {
-        launch_form_rhs(S.stream, L, r, u, f);  // no pre-smoothing launch to form it in
+        launch_form_rhs(S.stream, L, r, start, f);  // no pre-smoothing launch to form it in
+        launch_copy(S.stream, start, u, (int64_t)L.nx * L.ny);
+        start = u;
         r = nullptr;
     }
     if (l == S.L - 1) {
@@ -282,7 +288,7 @@ int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1
     const bool prof = S.profile && l == 0 && S.fused && nu1 > 0 && nu2 > 0 && !S.ev_pending;
     if (prof) FAS_HIP_CHECK(hipEventRecord(S.ev[0], S.stream));
     if (S.fused && nu1 > 0) {
-        cur = pre_fused(S.stream, S.loc, L, r, f, u, ut, nu1, C);
+        cur = pre_fused(S.stream, S.loc, L, r, f, start, u, ut, nu1, C);
         if (prof) FAS_HIP_CHECK(hipEventRecord(S.ev[1], S.stream));
         vcycle(S, l + 1, a, c, C.f, C.u, nu1, nu2, C.r);
     } else {

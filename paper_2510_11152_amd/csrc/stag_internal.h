@@ -21,10 +21,18 @@ struct Lev {
     double a, c, h2, ih2;
 };
 
-// Red-black sweep windows: 2 * kTile columns (a column pair per lane) x kWinRows rows in
-// LDS, nu sweeps (1 or 2) per launch.
+// Diagonals D = a h^2 + c k of a level's points: index 1 for a point at a wall of the x axis,
+// + 2 at a wall of the y axis (k = 4, + 1 per odd and - 1 per even ghost).
+struct PointCoef {
+    double D[4];
+};
+PointCoef point_coef(const Lev& L);
+
+// Red-black sweep windows: 2 * kTile columns (a column pair per lane) x kWinRows rows, four
+// rows per wave, nu sweeps (1 or 2) per launch.
 constexpr int kTile = 64;
-constexpr int kWinRows = 32;
+constexpr int kSweepWaves = 8;
+constexpr int kWinRows = 4 * kSweepWaves;
 constexpr int kNormBlocks = 1024;
 
 // The coarse iterate after the coarse solve and its restricted copy from before it: the FAS
@@ -42,16 +50,17 @@ struct Coarse {
 
 // Window of a sweep launch: rows, margins of the written region along x and y (the sweeps
 // reach 2 nu; the norm needs one more ring, the fused restriction two, since an edge axis
-// takes a third tap one past the region; x margins and the row margin of the restriction
-// stay even, keeping 2 x 2 blocks aligned), and the written extents.
+// takes a third tap one past the region, and the correction leaves the window's outermost
+// columns wrong; x margins and the row margin of the restriction stay even, keeping 2 x 2
+// blocks aligned), and the written extents.  Extents are even, so every window starts at an
+// even column and at rows of one parity.
 struct SweepGeom {
     int wy, hx, hy, ox, oy;
 };
-constexpr SweepGeom sweep_geom(int nu, bool norm, bool res)
+constexpr SweepGeom sweep_geom(int nu, bool corr, bool norm, bool res)
 {
-    return SweepGeom{kWinRows, 2 * nu + (norm || res ? 2 : 0),
-                     2 * nu + (res ? 2 : (norm ? 1 : 0)), 2 * kTile - 2 * (2 * nu + (norm || res ? 2 : 0)),
-                     kWinRows - 2 * (2 * nu + (res ? 2 : (norm ? 1 : 0)))};
+    const int hx = 2 * nu + (corr || norm || res ? 2 : 0), hy = 2 * nu + (res ? 2 : (norm ? 1 : 0));
+    return SweepGeom{kWinRows, hx, hy, 2 * kTile - 2 * hx, kWinRows - 2 * hy};
 }
 
 // Fused work of a sweep launch (flags), and its arrays.
@@ -60,8 +69,7 @@ struct SweepIO {
     Coarse C;           // SW_CORR: the window is loaded as uin + P e
     double* partials;   // SW_NORM: per block, the sum of the squared residuals written
     double* fout;       // SW_RHS: f (the input) holds r; f = r + L u is formed and written here
-    double* uc;         // SW_RES: uc = uc0 = R u and rc = R (f - L u) of the written region
-    double* uc0;
+    double* uc0;        // SW_RES: uc0 = R u and rc = R (f - L u) of the written region
     double* rc;
     int ncx, ncy;
 };
@@ -86,7 +94,8 @@ struct TailArgs {
     int nlev;                                   // levels in the tail (top first)
     Lev op[kTailMaxLevels];
     int ou[kTailMaxLevels], of[kTailMaxLevels], ou0[kTailMaxLevels];  // LDS offsets (doubles)
-    double* u;                                  // top level iterate (in and out)
+    const double* uin;                          // top level iterate
+    double* u;                                  // its new values
     const double* f;                            // top level right-hand side, or
     const double* r;                            // its restricted residual (f = r + L u formed here)
     int nu1, nu2, nuc;

@@ -1,0 +1,43 @@
+"""The staggered sweep windows at their edges, bit for bit against the oracle: levels whose
+width ends just before, at and after a window (128 columns, 116 to 120 written), with and
+without windows that touch no wall, and heights around the written rows."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import staggered as ost
+
+pytestmark = pytest.mark.gpu
+
+LOCS = [("cell", "neumann", ost.CELL), ("cell", "dirichlet", ost.CELL), ("edge_x", "dirichlet", ost.EDGE_X),
+        ("edge_y", "dirichlet", ost.EDGE_Y)]
+SIZES = [(8, 16), (116, 40), (120, 48), (124, 20), (128, 24), (232, 44), (248, 40), (250, 22), (360, 24), (376, 88)]
+
+
+@pytest.mark.parametrize("loc,bc,code", LOCS)
+@pytest.mark.parametrize("nx,ny", SIZES)
+@pytest.mark.parametrize("nu1,nu2", [(2, 2), (1, 1), (3, 3)])
+def test_window_edges_bitwise(loc, bc, code, nx, ny, nu1, nu2):
+    from paper_2510_11152_amd import StaggeredSolver
+    coarsest = ny
+    while coarsest % 2 == 0 and coarsest > 4 and nx % (2 * ny // coarsest) == 0:
+        coarsest //= 2
+    S = StaggeredSolver(loc, nx, ny, 1.0 / nx, bc=bc, coarsest=coarsest)
+    P = ost.StagProblem(code, nx, ny, 1.0 / nx, cell_bc=bc, coarsest=coarsest)
+    a, c = (0.0, 1.0) if bc == "neumann" else (1.0, 0.37)
+    rng = np.random.default_rng(nx * ny)
+    f, w = rng.standard_normal(P.shape()), rng.standard_normal(P.shape())
+    if a == 0.0:
+        f -= f.mean()
+    fd, wd = torch.from_numpy(f).cuda(), torch.from_numpy(w.copy()).cuda()
+    for _ in range(2):
+        S.vcycle(a, c, fd, wd, nu1, nu2)
+        ost.vcycle(P, a, c, f, w, nu1, nu2)
+    torch.cuda.synchronize()
+    assert np.array_equal(wd.cpu().numpy(), w)
+    if bc == "dirichlet":  # a whole solve: the norm of the last launch stops it
+        st, cyc, res = S.solve(a, c, fd, wd, 0.0, nu1, nu2, kmax=1)
+        ost.vcycle(P, a, c, f, w, nu1, nu2)
+        ref = ost.res_norm(P, a, c, f, w)
+        assert st == 1 and cyc == 1 and abs(res - ref) <= 1e-12 * ref
+        assert np.array_equal(wd.cpu().numpy(), w)
