@@ -517,95 +517,349 @@ __global__ __launch_bounds__(64 * kSweepWaves) void k_sweep(Lev L, PointCoef P, 
 }
 
 // ---- persistent coarse tail ------------------------------------------------------------------
-// One 1024-thread workgroup runs the V-cycle of the coarsest levels (top .. coarsest) with
+// One 512-thread workgroup runs the V-cycle of the coarsest levels (top .. coarsest) with
 // every array in LDS: the top level's iterate and right-hand side are loaded once and the
 // iterate is written back at the end, instead of five launches per level.  Each step uses
 // the point formulas of the per-level kernels, so the result is the same bit for bit.
-// The workgroup as 32 x 32 threads: (tx, ty) walks columns and rows with stride 32, so no
-// point index is divided by a row length.
-__device__ __forceinline__ int ttx() { return threadIdx.x & 31; }
-__device__ __forceinline__ int tty() { return threadIdx.x >> 5; }
+//
+// One compute unit issues everything, so a half-sweep costs its instructions on the large
+// levels and its latency chain on the small ones (the coarsest alone takes 32 half-sweeps).
+// As in the cell-centred tail, a thread owns blocks of 2 x 2 points (the last of an odd axis
+// is half a block whose missing points hold 0): half of a point's neighbours are the thread's
+// registers, the others come from LDS planes (one per point of a block, indexed by block,
+// index 0 a zero) at indices worked out once per visit of a level, and levels of at most 64
+// blocks run in one wave without block barriers.  With a point per thread and step, all
+// neighbours and diagonals worked out at each, 64^2 to 4^2 took 54.6 us (cells) and 59.5 us
+// (edges); now 29.1 and 32.1 us.
+constexpr int kTailThreads = 512;
 
-__device__ void tail_smooth(const Lev& L, const double* f, double* u, int nu)
-{
-    for (int sw = 0; sw < nu; ++sw) {
-        for (int colour = 1; colour >= 0; --colour) {  // sets 1-2 (odd index sum) first
-            for (int y = tty(); y < L.ny; y += 32) {
-                const int x0 = (colour + y) & 1;  // first column of this colour in row y
-                for (int x = x0 + 2 * ttx(); x < L.nx; x += 64) {
-                    const int t = y * L.nx + x;
-                    u[t] = (L.c * nbsum(L, u, x, y) + L.h2 * f[t]) / diag(L, x, y);
-                }
-            }
+__device__ __forceinline__ int div_by(int t, unsigned g) { return g ? (int)__umulhi((unsigned)t, g) : t; }
+
+// A thread's block on one level; point c is (c & 1, c >> 1).
+struct StagBlock {
+    bool on;
+    int o, I, J;
+    int nb[4];       // LDS indices of the blocks at x-, x+, y-, y+ (0: outside)
+    unsigned valid;  // points inside the level
+    bool bx[2], by[2];  // the points at 0 / 1 along x and y lie at a wall
+    double u[4], f[4], D[4];
+};
+
+template <int LOC, bool BIG>
+struct StagTail {
+    static constexpr int CAP = stag_tail_cap(BIG), CAP0 = stag_tail_cap0(BIG), KB = stag_tail_kb(BIG);
+    static_assert((size_t)(8 * CAP + 4 * CAP0) * sizeof(double) <= 160 * 1024, "LDS of one workgroup");
+    const TailArgs& a;
+    double* const lds;
+
+    __device__ __forceinline__ double* U(int c) const { return lds + c * CAP; }
+    __device__ __forceinline__ double* F(int c) const { return lds + (4 + c) * CAP; }
+
+    // Between steps that read what other threads wrote: a barrier, or inside one wave (whose
+    // LDS accesses are in order) only the compiler's order.
+    template <bool ONE>
+    static __device__ __forceinline__ void sync()
+    {
+        if constexpr (ONE) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        } else {
             __syncthreads();
         }
     }
-}
 
-template <int LOC>
-__global__ __launch_bounds__(1024) void k_tail(TailArgs A)
+    __device__ __forceinline__ void setup(const TailLev& L, int t, StagBlock& B) const
+    {
+        B.on = t < L.nb;
+        if (!B.on) t = 0;
+        B.J = div_by(t, L.g0);
+        B.I = t - B.J * L.m0;
+        B.o = L.off + t;
+        B.nb[0] = B.I > 0 ? B.o - 1 : 0;
+        B.nb[1] = B.I < L.m0 - 1 ? B.o + 1 : 0;
+        B.nb[2] = B.J > 0 ? B.o - L.m0 : 0;
+        B.nb[3] = B.J < L.m1 - 1 ? B.o + L.m0 : 0;
+        const bool x1 = 2 * B.I + 1 < L.nx, y1 = 2 * B.J + 1 < L.ny;
+        B.valid = 1u | (x1 ? 2u : 0u) | (y1 ? 4u : 0u) | (x1 && y1 ? 8u : 0u);
+        B.bx[0] = B.I == 0 || 2 * B.I == L.nx - 1;
+        B.bx[1] = 2 * B.I + 1 == L.nx - 1;
+        B.by[0] = B.J == 0 || 2 * B.J == L.ny - 1;
+        B.by[1] = 2 * B.J + 1 == L.ny - 1;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) B.D[c] = by_wall(B.bx[c & 1], B.by[c >> 1], L.D[0], L.D[1], L.D[2], L.D[3]);
+    }
+
+    // Neighbour sum of point c: inside the block from registers, else from LDS.
+    __device__ __forceinline__ double sum_of(const StagBlock& B, int c) const
+    {
+        const bool x = c & 1, y = c >> 1;
+        const int ox = c ^ 1, oy = c ^ 2;
+        const double W = x ? B.u[ox] : U(ox)[B.nb[0]], E = x ? U(ox)[B.nb[1]] : B.u[ox];
+        const double S = y ? B.u[oy] : U(oy)[B.nb[2]], N = y ? U(oy)[B.nb[3]] : B.u[oy];
+        return (W + E) + (S + N);
+    }
+    __device__ __forceinline__ double Lu(const TailLev& L, const StagBlock& B, int c) const
+    {
+        return (B.D[c] * B.u[c] - L.c * sum_of(B, c)) * L.ih2;
+    }
+
+    // One half-sweep: the points of index-sum parity P.
+    template <int P>
+    __device__ __forceinline__ void phase(const TailLev& L, StagBlock& B) const
+    {
+        constexpr int c0 = P, c1 = 3 - P;  // (P, 0) and (1 - P, 1)
+        const double v0 = (L.c * sum_of(B, c0) + L.h2 * B.f[c0]) / B.D[c0];
+        const double v1 = (L.c * sum_of(B, c1) + L.h2 * B.f[c1]) / B.D[c1];
+        B.u[c0] = B.valid >> c0 & 1 ? v0 : 0.0;
+        B.u[c1] = B.valid >> c1 & 1 ? v1 : 0.0;
+        U(c0)[B.o] = B.u[c0];
+        U(c1)[B.o] = B.u[c1];
+    }
+
+    template <int NB, bool ONE>
+    __device__ __forceinline__ void smooth(const TailLev& L, StagBlock (&B)[NB], int nu) const
+    {
+        for (int s = 0; s < nu; ++s) {
+            // sets 1-2 (odd index sum) first
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+                if (B[k].on) phase<1>(L, B[k]);
+            sync<ONE>();
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+                if (B[k].on) phase<0>(L, B[k]);
+            sync<ONE>();
+        }
+    }
+
+    // LDS plane offset and index of coarse point (K, J).
+    static __device__ __forceinline__ int cell_of(int K, int J) { return (K & 1) + 2 * (J & 1); }
+    static __device__ __forceinline__ int index_of(const TailLev& Lc, int K, int J)
+    {
+        return (K >> 1) + Lc.m0 * (J >> 1);
+    }
+
+    // Own points of every block: from LDS, or on the top level (gu != nullptr) from memory into
+    // registers and LDS.  Points that are not there become 0 in both.
+    template <int NB, bool ONE>
+    __device__ __forceinline__ void load(const TailLev& L, StagBlock (&B)[NB], const double* gu, const double* gf) const
+    {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) setup(L, (int)threadIdx.x + k * kTailThreads, B[k]);
+        if (gu) {
+            // every load of the thread is issued before the first use (missing points and
+            // blocks read a point that is there)
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int x = 2 * B[k].I + (B[k].valid & 2 ? c & 1 : 0), y = 2 * B[k].J + (B[k].valid & 4 ? c >> 1 : 0);
+                    B[k].u[c] = gu[y * L.nx + x];
+                    B[k].f[c] = gf[y * L.nx + x];
+                }
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (!B[k].on) continue;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (!gu) {
+                    B[k].u[c] = U(c)[B[k].o];
+                    B[k].f[c] = F(c)[B[k].o];
+                }
+                const bool in = B[k].valid >> c & 1;
+                B[k].u[c] = in ? B[k].u[c] : 0.0;
+                B[k].f[c] = in ? B[k].f[c] : 0.0;
+                if (gu || !in) {
+                    U(c)[B[k].o] = B[k].u[c];
+                    F(c)[B[k].o] = B[k].f[c];
+                }
+            }
+        }
+        if (gu) sync<ONE>();
+    }
+
+    // f = r + L u in place (the level's f holds r).
+    template <int NB, bool ONE>
+    __device__ __forceinline__ void form(const TailLev& L, StagBlock (&B)[NB]) const
+    {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (!B[k].on) continue;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                B[k].f[c] = B[k].f[c] + Lu(L, B[k], c);
+                F(c)[B[k].o] = B[k].f[c];
+            }
+        }
+        sync<ONE>();
+    }
+
+    // Down: pre-smoothing, then the restricted iterate and residual (as restrict_point).
+    template <int NB, bool ONE>
+    __device__ __forceinline__ void down(int lv, const double* gu, const double* gf) const
+    {
+        const TailLev& L = a.lev[lv];
+        const TailLev& Lc = a.lev[lv + 1];
+        StagBlock B[NB];
+        load<NB, ONE>(L, B, gu, gf);
+        if (lv > 0 || a.r) form<NB, ONE>(L, B);
+        smooth<NB, ONE>(L, B, a.nu1);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (!B[k].on || B[k].I >= Lc.nx || B[k].J >= Lc.ny) continue;
+            const StagBlock& b = B[k];
+            double r[4], ru, rr;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r[c] = b.f[c] - Lu(L, b, c);
+            if constexpr (LOC == LOC_CELL) {
+                ru = ((b.u[0] + b.u[1]) + (b.u[2] + b.u[3])) * 0.25;
+                rr = ((r[0] + r[1]) + (r[2] + r[3])) * 0.25;
+            } else if constexpr (LOC == LOC_EDGE_X) {
+                // the third tap: the first column of the block at x+
+                const int R = b.nb[1], Rm = b.nb[2] ? R - L.m0 : 0, Rp = b.nb[3] ? R + L.m0 : 0;
+                const bool wall = 2 * b.I + 2 == L.nx - 1;
+                double u2[2] = {U(0)[R], U(2)[R]}, r2[2];
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
+                    const double D = by_wall(wall, b.by[y], L.D[0], L.D[1], L.D[2], L.D[3]);
+                    const double s = (b.u[1 + 2 * y] + U(1 + 2 * y)[R]) +
+                                     (y ? u2[0] + U(0)[Rp] : U(2)[Rm] + u2[1]);
+                    r2[y] = F(2 * y)[R] - (D * u2[y] - L.c * s) * L.ih2;
+                }
+                ru = (((b.u[0] + 2.0 * b.u[1]) + u2[0]) + ((b.u[2] + 2.0 * b.u[3]) + u2[1])) * 0.125;
+                rr = (((r[0] + 2.0 * r[1]) + r2[0]) + ((r[2] + 2.0 * r[3]) + r2[1])) * 0.125;
+            } else {
+                // the third tap: the first row of the block at y+
+                const int A = b.nb[3], Am = b.nb[0] ? A - 1 : 0, Ap = b.nb[1] ? A + 1 : 0;
+                const bool wall = 2 * b.J + 2 == L.ny - 1;
+                double u2[2] = {U(0)[A], U(1)[A]}, r2[2];
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    const double D = by_wall(b.bx[x], wall, L.D[0], L.D[1], L.D[2], L.D[3]);
+                    const double s = (x ? u2[0] + U(0)[Ap] : U(1)[Am] + u2[1]) + (b.u[x + 2] + U(x + 2)[A]);
+                    r2[x] = F(x)[A] - (D * u2[x] - L.c * s) * L.ih2;
+                }
+                ru = (((b.u[0] + 2.0 * b.u[2]) + u2[0]) + ((b.u[1] + 2.0 * b.u[3]) + u2[1])) * 0.125;
+                rr = (((r[0] + 2.0 * r[2]) + r2[0]) + ((r[1] + 2.0 * r[3]) + r2[1])) * 0.125;
+            }
+            const int c = cell_of(b.I, b.J), p = index_of(Lc, b.I, b.J);
+            U(c)[Lc.off + p] = ru;
+            lds[8 * CAP + c * CAP0 + Lc.off0 + p] = ru;
+            F(c)[Lc.off + p] = rr;
+        }
+        sync<ONE>();
+    }
+
+    template <int NB, bool ONE>
+    __device__ __forceinline__ void coarsest(const double* gu, const double* gf, double* gout) const
+    {
+        const TailLev& L = a.lev[a.nlev - 1];
+        StagBlock B[NB];
+        load<NB, ONE>(L, B, gu, gf);
+        if (a.nlev > 1 || a.r) form<NB, ONE>(L, B);
+        smooth<NB, ONE>(L, B, a.nuc);  // Remark 1
+        if (gout) store<NB>(L, B, gout);
+    }
+
+    // Up: u += P (u_c - R u) (as prolong_point), post-smoothing.
+    template <int NB, bool ONE>
+    __device__ __forceinline__ void up(int lv, double* gout) const
+    {
+        const TailLev& L = a.lev[lv];
+        const TailLev& Lc = a.lev[lv + 1];
+        StagBlock B[NB];
+        load<NB, ONE>(L, B, nullptr, nullptr);
+        // e = uc - uc0 (out of range: a value that is not used)
+        auto e = [&](int K, int J) {
+            K = min(max(K, 0), Lc.nx - 1);
+            J = min(max(J, 0), Lc.ny - 1);
+            const int c = cell_of(K, J), p = index_of(Lc, K, J);
+            return lds[c * CAP + Lc.off + p] - lds[8 * CAP + c * CAP0 + Lc.off0 + p];
+        };
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (!B[k].on) continue;
+            const int K = B[k].I, J = B[k].J;
+            double p[4];
+            if constexpr (LOC == LOC_CELL) {
+                p[0] = p[1] = p[2] = p[3] = e(K, J);
+            } else if constexpr (LOC == LOC_EDGE_X) {
+                const double e0 = e(K, J), m = e(K - 1, J);
+                const double em = J > 0 ? e(K, J - 1) : -e0, mm = J > 0 ? e(K - 1, J - 1) : -m;
+                const double ep = J < Lc.ny - 1 ? e(K, J + 1) : -e0, mp = J < Lc.ny - 1 ? e(K - 1, J + 1) : -m;
+                const bool l = K >= 1, r = K <= Lc.nx - 1;
+                p[1] = lin_cell(e0, em);
+                p[3] = lin_cell(e0, ep);
+                p[0] = ((l ? lin_cell(m, mm) : 0.0) + (r ? p[1] : 0.0)) * 0.5;
+                p[2] = ((l ? lin_cell(m, mp) : 0.0) + (r ? p[3] : 0.0)) * 0.5;
+            } else {
+                const double e0 = e(K, J), m = e(K, J - 1);
+                const double em = K > 0 ? e(K - 1, J) : -e0, mm = K > 0 ? e(K - 1, J - 1) : -m;
+                const double ep = K < Lc.nx - 1 ? e(K + 1, J) : -e0, mp = K < Lc.nx - 1 ? e(K + 1, J - 1) : -m;
+                const bool b = J >= 1, t = J <= Lc.ny - 1;
+                p[2] = lin_cell(e0, em);
+                p[3] = lin_cell(e0, ep);
+                p[0] = ((b ? lin_cell(m, mm) : 0.0) + (t ? p[2] : 0.0)) * 0.5;
+                p[1] = ((b ? lin_cell(m, mp) : 0.0) + (t ? p[3] : 0.0)) * 0.5;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                B[k].u[c] = B[k].valid >> c & 1 ? B[k].u[c] + p[c] : 0.0;
+                U(c)[B[k].o] = B[k].u[c];
+            }
+        }
+        sync<ONE>();
+        smooth<NB, ONE>(L, B, a.nu2);
+        if (gout) store<NB>(L, B, gout);
+    }
+
+    template <int NB>
+    __device__ __forceinline__ void store(const TailLev& L, StagBlock (&B)[NB], double* gout) const
+    {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (!B[k].on) continue;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (B[k].valid >> c & 1) gout[(2 * B[k].J + (c >> 1)) * L.nx + 2 * B[k].I + (c & 1)] = B[k].u[c];
+        }
+    }
+
+    __device__ __forceinline__ void run() const
+    {
+        const int last = a.nlev - 1;
+        const double* const gf = a.r ? a.r : a.f;
+        if (threadIdx.x < 4) U((int)threadIdx.x)[0] = 0.0;
+        __syncthreads();
+        // blocks per level fall, so one wave runs the levels from a.one on
+        for (int l = 0; l < a.one && l < last; ++l) down<KB, false>(l, l ? nullptr : a.uin, gf);
+        if (a.one < a.nlev) {
+            if (threadIdx.x < 64) {
+                for (int l = a.one; l < last; ++l) down<1, true>(l, l ? nullptr : a.uin, gf);
+                coarsest<1, true>(last ? nullptr : a.uin, gf, last ? nullptr : a.u);
+                for (int l = last - 1; l >= a.one; --l) up<1, true>(l, l ? nullptr : a.u);
+            }
+            __syncthreads();
+        } else {
+            coarsest<KB, false>(last ? nullptr : a.uin, gf, last ? nullptr : a.u);
+        }
+        for (int l = (a.one < last ? a.one : last) - 1; l >= 0; --l) up<KB, false>(l, l ? nullptr : a.u);
+    }
+};
+
+template <int LOC, bool BIG>
+__global__ __launch_bounds__(kTailThreads) void k_tail(TailArgs args)
 {
-    __shared__ double lds[kTailDoubles];
-    const int n0 = A.op[0].nx * A.op[0].ny;
-    for (int t = threadIdx.x; t < n0; t += blockDim.x) {
-        lds[A.ou[0] + t] = A.uin[t];
-        lds[A.of[0] + t] = A.r ? A.r[t] : A.f[t];
-    }
-    __syncthreads();
-    if (A.r) {
-        // f = r + L u from the loaded iterate (as k_coarse_rhs)
-        const Lev& L = A.op[0];
-        double* u = lds + A.ou[0];
-        double* f = lds + A.of[0];
-        // f at a point depends on r only at that point: formed in place
-        for (int y = tty(); y < L.ny; y += 32)
-            for (int x = ttx(); x < L.nx; x += 32) {
-                const int t = y * L.nx + x;
-                f[t] = f[t] + (diag(L, x, y) * u[t] - L.c * nbsum(L, u, x, y)) * L.ih2;
-            }
-        __syncthreads();
-    }
-    for (int l = 0; l + 1 < A.nlev; ++l) {
-        const Lev& L = A.op[l];
-        const Lev& Lc = A.op[l + 1];
-        double* u = lds + A.ou[l];
-        const double* f = lds + A.of[l];
-        tail_smooth(L, f, u, A.nu1);
-        double* uc = lds + A.ou[l + 1];
-        double* uc0 = lds + A.ou0[l + 1];
-        double* fc = lds + A.of[l + 1];
-        for (int J = tty(); J < Lc.ny; J += 32)
-            for (int K = ttx(); K < Lc.nx; K += 32) {
-                double ru, rr;
-                restrict_point<LOC>(L, f, u, K, J, ru, rr);
-                const int t = J * Lc.nx + K;
-                uc[t] = ru;
-                uc0[t] = ru;
-                fc[t] = rr;
-            }
-        __syncthreads();
-        for (int y = tty(); y < Lc.ny; y += 32)
-            for (int x = ttx(); x < Lc.nx; x += 32) {
-                const int t = y * Lc.nx + x;
-                fc[t] = fc[t] + (diag(Lc, x, y) * uc[t] - Lc.c * nbsum(Lc, uc, x, y)) * Lc.ih2;
-            }
-        __syncthreads();
-    }
-    const int lc = A.nlev - 1;
-    tail_smooth(A.op[lc], lds + A.of[lc], lds + A.ou[lc], A.nuc);  // Remark 1
-    for (int l = A.nlev - 2; l >= 0; --l) {
-        const Lev& L = A.op[l];
-        const Coarse C{lds + A.ou[l + 1], lds + A.ou0[l + 1], A.op[l + 1].nx, A.op[l + 1].ny};
-        double* u = lds + A.ou[l];
-        for (int y = tty(); y < L.ny; y += 32)
-            for (int x = ttx(); x < L.nx; x += 32) {
-                const int t = y * L.nx + x;
-                u[t] = u[t] + prolong_point<LOC>(C, x, y);
-            }
-        __syncthreads();
-        tail_smooth(L, lds + A.of[l], u, A.nu2);
-    }
-    for (int t = threadIdx.x; t < n0; t += blockDim.x) A.u[t] = lds[A.ou[0] + t];
+    // levels are picked at run time: read the arguments where they are, as constants (a copy
+    // would go through scratch)
+    (void)args;
+    const TailArgs& a =
+        *(const TailArgs*)(const __attribute__((address_space(4))) TailArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    using Tl = StagTail<LOC, BIG>;
+    __shared__ double lds[8 * Tl::CAP + 4 * Tl::CAP0];
+    const Tl tail{a, lds};
+    tail.run();
 }
 
 // ---- residual norm -------------------------------------------------------------------------
@@ -876,14 +1130,76 @@ void launch_sum(hipStream_t s, const double* partials, int n, double* out)
     hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, partials, n, out);
 }
 
-void launch_tail(hipStream_t s, int loc, const TailArgs& A)
+TailLev tail_lev(const Lev& L)
 {
+    TailLev T{};
+    T.nx = L.nx;
+    T.ny = L.ny;
+    T.m0 = (L.nx + 1) / 2;
+    T.m1 = (L.ny + 1) / 2;
+    T.nb = T.m0 * T.m1;
+    T.g0 = T.m0 > 1 ? (unsigned)((((uint64_t)1 << 32) + (uint64_t)T.m0 - 1) / (uint64_t)T.m0) : 0u;
+    T.c = L.c;
+    T.h2 = L.h2;
+    T.ih2 = L.ih2;
+    const PointCoef P = point_coef(L);
+    for (int i = 0; i < 4; ++i) T.D[i] = P.D[i];
+    return T;
+}
+
+// LDS layout of the levels in A.lev (their off, off0) and the first level one wave runs;
+// returns whether it takes the small (0) or the big (1) planes, or -1 when neither hold it.
+namespace {
+int tail_class(TailArgs& A)
+{
+    int off = 1, off0 = 0;  // block 0: the zeros outside the grid
+    A.one = A.nlev;
+    for (int k = 0; k < A.nlev; ++k) {
+        A.lev[k].off = off;
+        A.lev[k].off0 = off0;
+        off += A.lev[k].nb;
+        if (k > 0) off0 += A.lev[k].nb;  // the top level keeps no restricted copy
+        if (A.lev[k].nb <= 64 && A.one == A.nlev) A.one = k;
+    }
+    for (int big = 0; big < 2; ++big)
+        if (off <= stag_tail_cap(big) && off0 <= stag_tail_cap0(big) &&
+            A.lev[0].nb <= kTailThreads * stag_tail_kb(big))
+            return big;
+    return -1;
+}
+}  // namespace
+
+bool tail_fits(const int* nx, const int* ny, int nlev)
+{
+    TailArgs A{};
+    A.nlev = nlev;
+    for (int k = 0; k < nlev; ++k) {
+        Lev L{};
+        L.nx = nx[k];
+        L.ny = ny[k];
+        A.lev[k] = tail_lev(L);
+    }
+    return tail_class(A) >= 0;
+}
+
+void launch_tail(hipStream_t s, int loc, TailArgs& A)
+{
+    const int big = tail_class(A);
+    if (big < 0) throw Error(FAS_ERR_ARG, "internal: tail levels exceed the tail's LDS");
+#define FAS_STAG_TAIL(LOC_)                                                                              \
+    do {                                                                                                 \
+        if (big)                                                                                         \
+            hipLaunchKernelGGL((k_tail<LOC_, true>), dim3(1), dim3(kTailThreads), 0, s, A);              \
+        else                                                                                             \
+            hipLaunchKernelGGL((k_tail<LOC_, false>), dim3(1), dim3(kTailThreads), 0, s, A);             \
+    } while (0)
     if (loc == LOC_CELL)
-        hipLaunchKernelGGL(k_tail<LOC_CELL>, dim3(1), dim3(1024), 0, s, A);
+        FAS_STAG_TAIL(LOC_CELL);
     else if (loc == LOC_EDGE_X)
-        hipLaunchKernelGGL(k_tail<LOC_EDGE_X>, dim3(1), dim3(1024), 0, s, A);
+        FAS_STAG_TAIL(LOC_EDGE_X);
     else
-        hipLaunchKernelGGL(k_tail<LOC_EDGE_Y>, dim3(1), dim3(1024), 0, s, A);
+        FAS_STAG_TAIL(LOC_EDGE_Y);
+#undef FAS_STAG_TAIL
 }
 
 void launch_restrict(hipStream_t s, int loc, const Lev& Lf, const double* f, const double* u, int ncx, int ncy,

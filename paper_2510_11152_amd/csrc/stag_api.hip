@@ -20,7 +20,6 @@ struct fas_stag {
     int fused;      // 1: persistent tail for the coarse levels and the correction fused into
                     // the first post-smoothing launch; 0: one kernel per step and level
     int tail_top;   // first level of the persistent tail
-    int tail_ou[fas::stag::kTailMaxLevels], tail_of[fas::stag::kTailMaxLevels], tail_ou0[fas::stag::kTailMaxLevels];
     int kx, ky;
     int64_t mx, my;  // cells of the finest level
     double h;
@@ -257,12 +256,7 @@ int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1
     if (S.fused && l == S.tail_top) {
         TailArgs A{};
         A.nlev = S.L - l;
-        for (int k = 0; k < A.nlev; ++k) {
-            A.op[k] = level_op(S, l + k, a, c);
-            A.ou[k] = S.tail_ou[k];
-            A.of[k] = S.tail_of[k];
-            A.ou0[k] = S.tail_ou0[k];
-        }
+        for (int k = 0; k < A.nlev; ++k) A.lev[k] = tail_lev(level_op(S, l + k, a, c));
         A.uin = start;
         A.u = u;
         A.f = f;
@@ -424,17 +418,13 @@ void init_stag(fas_stag& S, int loc, int64_t mx, int64_t my, double h, int cell_
     S.tail_top = -1;
     for (int top = 0; top < S.L; ++top) {
         if ((int64_t)S.lev[top].nx * S.lev[top].ny > kTailTopMax || S.L - top > kTailMaxLevels) continue;
-        int need = 0;
-        for (int l = top; l < S.L; ++l) need += (l == top ? 2 : 3) * S.lev[l].nx * S.lev[l].ny;
-        if (need > kTailDoubles) continue;
-        int o = 0;
+        int need = 0, nx[kTailMaxLevels], ny[kTailMaxLevels];
         for (int l = top; l < S.L; ++l) {
-            const int n = S.lev[l].nx * S.lev[l].ny, k = l - top;
-            S.tail_ou[k] = o;
-            S.tail_of[k] = o + n;
-            S.tail_ou0[k] = l == top ? -1 : o + 2 * n;
-            o += (l == top ? 2 : 3) * n;
+            need += (l == top ? 2 : 3) * S.lev[l].nx * S.lev[l].ny;
+            nx[l - top] = S.lev[l].nx;
+            ny[l - top] = S.lev[l].ny;
         }
+        if (need > kTailDoubles || !tail_fits(nx, ny, S.L - top)) continue;
         S.tail_top = top;
         break;
     }

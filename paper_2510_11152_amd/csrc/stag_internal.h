@@ -86,21 +86,40 @@ void launch_sum(hipStream_t s, const double* partials, int n, double* out);
 // f = r + L u on level L (out of place).
 void launch_form_rhs(hipStream_t s, const Lev& L, const double* r, const double* u, double* f);
 
-// Persistent tail: levels top .. coarsest in one workgroup's LDS.
+// Persistent tail: levels top .. coarsest in one workgroup's LDS, as blocks of 2 x 2 points
+// (kernels_stag.hip).
 constexpr int kTailMaxLevels = 12;
-constexpr int kTailDoubles = 16384;  // 128 KiB of LDS
-constexpr int kTailTopMax = 4096;    // unknowns of the tail's top level (4 per thread)
+constexpr int kTailDoubles = 16384;  // most unknowns of the tail's arrays (iterate, right-hand
+                                     // side and, below the top, the restricted iterate)
+constexpr int kTailTopMax = 4096;    // unknowns of the tail's top level
+// Blocks a plane of the iterate / right-hand side and one of the restricted iterate hold, and
+// blocks a thread owns on the top level.  Small: 64 x 64 points at the top; big: levels of one
+// or two rows, where most blocks are half empty.
+constexpr int stag_tail_cap(bool big) { return big ? 2064 : 1368; }
+constexpr int stag_tail_cap0(bool big) { return big ? 688 : 352; }
+constexpr int stag_tail_kb(bool big) { return big ? 5 : 2; }
+struct TailLev {
+    int nx, ny;      // unknowns
+    int m0, m1, nb;  // blocks along x and y, and in all
+    int off, off0;   // the level's first block in the planes
+    unsigned g0;     // ceil(2^32 / m0) (0: m0 is one)
+    double c, h2, ih2, D[4];  // as Lev and PointCoef
+};
 struct TailArgs {
-    int nlev;                                   // levels in the tail (top first)
-    Lev op[kTailMaxLevels];
-    int ou[kTailMaxLevels], of[kTailMaxLevels], ou0[kTailMaxLevels];  // LDS offsets (doubles)
-    const double* uin;                          // top level iterate
-    double* u;                                  // its new values
-    const double* f;                            // top level right-hand side, or
-    const double* r;                            // its restricted residual (f = r + L u formed here)
+    int nlev;         // levels in the tail (top first)
+    int one;          // first level run by a single wave (nlev: none)
+    TailLev lev[kTailMaxLevels];
+    const double* uin;  // top level iterate
+    double* u;          // its new values
+    const double* f;    // top level right-hand side, or
+    const double* r;    // its restricted residual (f = r + L u formed here)
     int nu1, nu2, nuc;
 };
-void launch_tail(hipStream_t s, int loc, const TailArgs& A);
+TailLev tail_lev(const Lev& L);
+// Sets A's layout (lev[].off, lev[].off0, one) and launches it.
+void launch_tail(hipStream_t s, int loc, TailArgs& A);
+// Whether the tail can hold levels of these unknowns (nlev of them, finest first).
+bool tail_fits(const int* nx, const int* ny, int nlev);
 // Coarse iterate, its copy and the restricted residual of fine level Lf (location loc):
 // uc = uc0 = R u, rc = R (f - L u); coarse sizes ncx x ncy.
 void launch_restrict(hipStream_t s, int loc, const Lev& Lf, const double* f, const double* u, int ncx, int ncy,

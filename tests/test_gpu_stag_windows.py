@@ -41,3 +41,28 @@ def test_window_edges_bitwise(loc, bc, code, nx, ny, nu1, nu2):
         ref = ost.res_norm(P, a, c, f, w)
         assert st == 1 and cyc == 1 and abs(res - ref) <= 1e-12 * ref
         assert np.array_equal(wd.cpu().numpy(), w)
+
+
+# (nx, ny, coarsest): the tail alone or nearly so, from one block to rows of half blocks
+TAILS = [(4, 4, 2), (8, 8, 4), (10, 6, 3), (16, 16, 2), (20, 12, 3), (32, 32, 4), (34, 32, 16), (64, 64, 4), (68, 60, 15),
+         (128, 128, 4), (1024, 16, 2), (1364, 8, 2), (4096, 4, 2), (8192, 4, 2)]
+
+
+@pytest.mark.parametrize("loc,bc,code", LOCS)
+@pytest.mark.parametrize("nx,ny,coarsest", TAILS)
+def test_tail_levels_bitwise(loc, bc, code, nx, ny, coarsest):
+    from paper_2510_11152_amd import StaggeredSolver
+    S = StaggeredSolver(loc, nx, ny, 1.0 / nx, bc=bc, coarsest=coarsest)
+    S.set(coarse_sweeps=3)
+    P = ost.StagProblem(code, nx, ny, 1.0 / nx, cell_bc=bc, coarsest=coarsest, nuc=3)
+    a, c = (0.0, 1.0) if bc == "neumann" else (1.0, 0.37)
+    rng = np.random.default_rng(nx + ny)
+    f, w = rng.standard_normal(P.shape()), rng.standard_normal(P.shape())
+    if a == 0.0:
+        f -= f.mean()
+    fd, wd = torch.from_numpy(f).cuda(), torch.from_numpy(w.copy()).cuda()
+    for nu1, nu2 in ((2, 2), (1, 0), (0, 3)):
+        S.vcycle(a, c, fd, wd, nu1, nu2)
+        ost.vcycle(P, a, c, f, w, nu1, nu2)
+        torch.cuda.synchronize()
+        assert np.array_equal(wd.cpu().numpy(), w), (nu1, nu2)
