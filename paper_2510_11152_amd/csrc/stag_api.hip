@@ -33,7 +33,10 @@ struct fas_stag {
         double* r;        // restricted residual of the finer level (levels >= 1, fused path)
     } lev[fas::kMaxLevels];
     double* partials;
-    double* norm;
+    double* norm;      // 8 doubles: a norm, or the Status of a solve (device)
+    Status* host;      // pinned copy of the Status, allocated by the first solve that needs it
+    const int* act;    // inside such a solve: its active flag, which every launch of a cycle checks
+    int last_cycles, prev_cycles;  // cycles of the last two converged solves (0: none)
     hipStream_t stream;
     // FAS_OPT_PROFILE: HIP events around the finest level's pre- and post-smoothing launches
     int profile;
@@ -158,7 +161,8 @@ Lev level_op(const fas_stag& S, int l, double a, double c)
 // applied as the first launch loads its window; partials: the last launch sums the residual
 // norm (its block count goes to norm_blocks).  Returns the buffer that holds the result.
 double* sweeps(hipStream_t st, int loc, const Lev& L, const double* f, double* cur, double* alt, int nu, double* want,
-               const Coarse* corr = nullptr, double* partials = nullptr, int* norm_blocks = nullptr)
+               const Coarse* corr = nullptr, double* partials = nullptr, int* norm_blocks = nullptr,
+               const int* act = nullptr)
 {
     if (nu <= 0) {
         if (want && want != cur) {
@@ -187,6 +191,7 @@ double* sweeps(hipStream_t st, int loc, const Lev& L, const double* f, double* c
     for (int i = 0; i < n; ++i) {
         const bool last = i == n - 1 && !copy_after;
         SweepIO io{};
+        io.act = act;
         unsigned flags = 0;
         if (i == 0 && corr) {
             io.C = *corr;
@@ -215,13 +220,14 @@ int launches(int nu) { return nu / 2 + nu % 2; }
 // smoothed iterate and its residual into level C.  Returns the buffer holding the smoothed
 // iterate.
 double* pre_fused(hipStream_t st, int loc, const Lev& L, const double* r, double* f, const double* start, double* u,
-                  double* ut, int nu, fas_stag::Level& C)
+                  double* ut, int nu, fas_stag::Level& C, const int* act)
 {
     const int twos = nu / 2, n = twos + nu % 2;
     const double* a = start;
     double* b = start == ut ? u : ut;
     for (int i = 0; i < n; ++i) {
         SweepIO io{};
+        io.act = act;
         unsigned flags = 0;
         const double* fin = f;
         if (i == 0 && r) {
@@ -264,6 +270,7 @@ int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1
         A.nu1 = nu1;
         A.nu2 = nu2;
         A.nuc = S.nuc;
+        A.act = S.act;
         launch_tail(S.stream, S.loc, A);
         return 0;
     }
@@ -282,7 +289,7 @@ int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1
     const bool prof = S.profile && l == 0 && S.fused && nu1 > 0 && nu2 > 0 && !S.ev_pending;
     if (prof) FAS_HIP_CHECK(hipEventRecord(S.ev[0], S.stream));
     if (S.fused && nu1 > 0) {
-        cur = pre_fused(S.stream, S.loc, L, r, f, start, u, ut, nu1, C);
+        cur = pre_fused(S.stream, S.loc, L, r, f, start, u, ut, nu1, C, S.act);
         if (prof) FAS_HIP_CHECK(hipEventRecord(S.ev[1], S.stream));
         vcycle(S, l + 1, a, c, C.f, C.u, nu1, nu2, C.r);
     } else {
@@ -297,7 +304,8 @@ int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1
         const Coarse corr{C.u, C.u0, C.nx, C.ny};
         int nb = 0;
         if (prof) FAS_HIP_CHECK(hipEventRecord(S.ev[2], S.stream));
-        sweeps(S.stream, S.loc, L, f, cur, cur == u ? ut : u, nu2, u, &corr, l == 0 ? S.partials : nullptr, &nb);
+        sweeps(S.stream, S.loc, L, f, cur, cur == u ? ut : u, nu2, u, &corr, l == 0 ? S.partials : nullptr, &nb,
+               S.act);
         if (prof) {
             FAS_HIP_CHECK(hipEventRecord(S.ev[3], S.stream));
             S.ev_pending = true;
@@ -324,15 +332,6 @@ void profile_collect(fas_stag& S)
     S.ev_pending = false;
 }
 
-double read_norm(fas_stag& S)
-{
-    double s2 = 0.0;
-    FAS_HIP_CHECK(hipMemcpyAsync(&s2, S.norm, sizeof(double), hipMemcpyDeviceToHost, S.stream));
-    FAS_HIP_CHECK(hipStreamSynchronize(S.stream));
-    profile_collect(S);
-    return S.h * sqrt(s2);
-}
-
 double residual_norm(fas_stag& S, double a, double c, const double* f, const double* u, double* r)
 {
     const Lev L = level_op(S, 0, a, c);
@@ -350,19 +349,80 @@ void check_pointers(const void* f, const void* u)
     if (f == u) throw Error(FAS_ERR_ARG, "f and w must not alias");
 }
 
+// Whether a V(nu1, nu2) cycle leaves the norm's partial sums behind and all its launches that
+// write the finest iterate check the active flag: one post-smoothing launch, from the second
+// buffer into u.
+bool norm_in_cycle(const fas_stag& S, int nu1, int nu2)
+{
+    return S.fused && S.L > 1 && S.tail_top != 0 && nu1 > 0 && launches(nu1) % 2 == 1 && (nu2 == 1 || nu2 == 2);
+}
+
+// The largest s2 with h sqrt(s2) <= tol in double arithmetic (-1: none), so that a test of s2
+// on the device stops at the cycle at which a test of the norm would.
+double s2_limit(double h, double tol)
+{
+    auto stops = [&](double s2) { return h * sqrt(s2) <= tol; };
+    if (!stops(0.0)) return -1.0;
+    double x = (tol / h) * (tol / h);
+    if (!isfinite(x)) x = 1.7976931348623157e308;
+    while (!stops(x)) x = nextafter(x, 0.0);
+    while (x < 1.7976931348623157e308 && stops(nextafter(x, INFINITY))) x = nextafter(x, INFINITY);
+    return x;
+}
+
+// The solve with the stopping test on the device: a result that the host looks at stalls the
+// GPU for tens of microseconds, so after solves that took the same number of cycles that many
+// are enqueued before the first look (the fewer, if the last two solves differ; profiling
+// looks at every cycle).  Cycles enqueued after the stop do nothing, so the iterate, the
+// number of cycles and the norm do not depend on this.  Returns the cycles and the norm.
+void solve_looped(fas_stag& S, double a, double c, const double* f, double* u, double tol, int nu1, int nu2, int kmax,
+                  int& k_out, double& res_out)
+{
+    if (!S.host) FAS_HIP_CHECK(hipHostMalloc((void**)&S.host, sizeof(Status), hipHostMallocDefault));
+    Status* const dev = reinterpret_cast<Status*>(S.norm);
+    const double s2max = s2_limit(S.h, tol);
+    const Lev L = level_op(S, 0, a, c);
+    launch_status(S.stream, S.partials, launch_resnorm_partials(S.stream, L, f, u, nullptr, S.partials), s2max, 0, dev);
+    struct Gate {
+        fas_stag& S;
+        ~Gate() { S.act = nullptr; }
+    } gate{S};
+    S.act = &dev->act;
+    const int horizon = S.profile ? 0 : std::min(S.last_cycles, S.prev_cycles);
+    S.prev_cycles = S.last_cycles;
+    S.last_cycles = 0;
+    int k = 0;
+    for (;; ++k) {
+        if (k >= horizon || k >= kmax) {
+            FAS_HIP_CHECK(hipMemcpyAsync(S.host, dev, sizeof(Status), hipMemcpyDeviceToHost, S.stream));
+            FAS_HIP_CHECK(hipStreamSynchronize(S.stream));
+            profile_collect(S);
+            if (!S.host->act || k >= kmax) break;
+        }
+        const int nb = vcycle(S, 0, a, c, const_cast<double*>(f), u, nu1, nu2);
+        if (nb <= 0) throw Error(FAS_ERR_ARG, "internal: a cycle without its norm");
+        launch_status(S.stream, S.partials, nb, s2max, k + 1, dev);
+    }
+    // (still active at kmax: every cycle enqueued ran)
+    if (!S.host->act) k = S.host->cyc < 0 ? -1 - S.host->cyc : S.host->cyc;
+    k_out = k;
+    res_out = S.h * sqrt(S.host->s2);
+    if (res_out <= tol) S.last_cycles = k;
+}
+
 int solve(fas_stag& S, double a, double c, const double* f, double* u, double tol, int nu1, int nu2, int kmax,
           int* cycles_out, double* res_out)
 {
     if (nu1 < 0 || nu2 < 0 || kmax < 0 || !(tol >= 0.0)) throw Error(FAS_ERR_ARG, "bad nu1, nu2, kmax or tol");
-    double res = residual_norm(S, a, c, f, u, nullptr);
     int k = 0;
-    while (isfinite(res) && res > tol && k < kmax) {
-        const int nb = vcycle(S, 0, a, c, const_cast<double*>(f), u, nu1, nu2);
-        ++k;
-        if (nb > 0) {
-            launch_sum(S.stream, S.partials, nb, S.norm);
-            res = read_norm(S);
-        } else {
+    double res;
+    if (norm_in_cycle(S, nu1, nu2)) {
+        solve_looped(S, a, c, f, u, tol, nu1, nu2, kmax, k, res);
+    } else {
+        res = residual_norm(S, a, c, f, u, nullptr);
+        while (isfinite(res) && res > tol && k < kmax) {
+            vcycle(S, 0, a, c, const_cast<double*>(f), u, nu1, nu2);
+            ++k;
             res = residual_norm(S, a, c, f, u, nullptr);
         }
     }
@@ -454,8 +514,10 @@ int set_option(fas_stag& S, int option, double value)
     return FAS_OK;
 }
 
-void release_events(fas_stag* s)
+void release_host(fas_stag* s)
 {
+    if (s && s->host) (void)hipHostFree(s->host);
+    if (s) s->host = nullptr;
     if (s && s->ev[0])
         for (auto& e : s->ev) {
             (void)hipEventDestroy(e);
@@ -499,7 +561,7 @@ int fas_stag_create(int loc, int64_t nx, int64_t ny, double h, int cell_bc, int 
 
 int fas_stag_destroy(fas_stag_t* s)
 {
-    release_events(s);
+    release_host(s);
     delete s;
     return FAS_OK;
 }
@@ -640,9 +702,9 @@ int fas_ns_create(int64_t nx, int64_t ny, double h, double re, int layout, int c
 int fas_ns_destroy(fas_ns_t* ns)
 {
     if (ns) {
-        release_events(ns->su);
-        release_events(ns->sv);
-        release_events(ns->sp);
+        release_host(ns->su);
+        release_host(ns->sv);
+        release_host(ns->sp);
         delete ns->su;
         delete ns->sv;
         delete ns->sp;

@@ -69,6 +69,7 @@ struct SweepIO {
     Coarse C;           // SW_CORR: the window is loaded as uin + P e
     double* partials;   // SW_NORM: per block, the sum of the squared residuals written
     double* fout;       // SW_RHS: f (the input) holds r; f = r + L u is formed and written here
+    const int* act;     // nullable: the solve's active flag (0: the launch does nothing)
     double* uc0;        // SW_RES: uc0 = R u and rc = R (f - L u) of the written region
     double* rc;
     int ncx, ncy;
@@ -81,8 +82,16 @@ int launch_sweep(hipStream_t s, int loc, const Lev& L, int nu, const double* f, 
                  const SweepIO& io, unsigned flags);
 // Blocks of such a launch (tiles_x may be NULL).
 int sweep_blocks(const Lev& L, int nu, unsigned flags, int* tiles_x);
-// out[0] = sum of partials[0 .. n) in a fixed order.
-void launch_sum(hipStream_t s, const double* partials, int n, double* out);
+// State of a solve whose stopping test runs on the device.
+struct Status {
+    double s2;  // ||f - L u||^2 after the last cycle that ran
+    int act;    // 1: still iterating
+    int cyc;    // cycles of the stop, or -1 - cycles if the norm is not finite
+};
+// s2 = sum of partials[0 .. n) in a fixed order, then the stopping test after cycle k (0: the
+// initial residual, which starts the solve): active while s2 is finite and > s2max.  Does
+// nothing (k > 0) once the solve has stopped.
+void launch_status(hipStream_t s, const double* partials, int n, double s2max, int k, Status* st);
 // f = r + L u on level L (out of place).
 void launch_form_rhs(hipStream_t s, const Lev& L, const double* r, const double* u, double* f);
 
@@ -114,6 +123,7 @@ struct TailArgs {
     const double* f;    // top level right-hand side, or
     const double* r;    // its restricted residual (f = r + L u formed here)
     int nu1, nu2, nuc;
+    const int* act;     // nullable: the solve's active flag
 };
 TailLev tail_lev(const Lev& L);
 // Sets A's layout (lev[].off, lev[].off0, one) and launches it.
@@ -132,6 +142,8 @@ void launch_correct(hipStream_t s, int loc, const Lev& Lf, const double* uc, con
 // sum (f - L u)^2 into out[0] (fixed order); r (optional) receives the residual.
 void launch_resnorm(hipStream_t s, const Lev& L, const double* f, const double* u, double* r, double* partials,
                     double* out);
+// The partial sums alone; returns their number.
+int launch_resnorm_partials(hipStream_t s, const Lev& L, const double* f, const double* u, double* r, double* partials);
 void launch_copy(hipStream_t s, const double* src, double* dst, int64_t n);
 
 // ---- projection step (Section 4.2) ---------------------------------------------------------

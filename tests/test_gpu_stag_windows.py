@@ -66,3 +66,38 @@ def test_tail_levels_bitwise(loc, bc, code, nx, ny, coarsest):
         ost.vcycle(P, a, c, f, w, nu1, nu2)
         torch.cuda.synchronize()
         assert np.array_equal(wd.cpu().numpy(), w), (nu1, nu2)
+
+
+@pytest.mark.parametrize("loc,bc,code", LOCS)
+@pytest.mark.parametrize("nu1,nu2", [(2, 2), (1, 1), (5, 2), (3, 2)])
+def test_solve_does_not_depend_on_earlier_solves(loc, bc, code, nu1, nu2):
+    """Cycles enqueued on the strength of earlier solves do nothing once a solve has stopped:
+    a short solve, one already converged, one cut off by kmax and one that is not finite give
+    what a fresh solver gives, after two longer solves."""
+    from paper_2510_11152_amd import StaggeredSolver
+    from paper_2510_11152_amd._lib import FasError
+
+    def make():
+        return StaggeredSolver(loc, 256, 128, 1.0 / 256, bc=bc)
+
+    S = make()
+    a, c = (0.0, 1.0) if bc == "neumann" else (1.0, 0.37)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    f = torch.rand(S.shape, dtype=torch.float64, device="cuda", generator=g)
+    f -= f.mean()
+    w0 = torch.rand(S.shape, dtype=torch.float64, device="cuda", generator=g)
+    for tol, kmax in ((1e-3, 20), (1e9, 20), (1e-9, 2), (1e-9, 20)):
+        fresh, w1 = make(), w0.clone()
+        want = fresh.solve(a, c, f, w1, tol, nu1, nu2, kmax)
+        S = make()
+        for _ in range(2):
+            S.solve(a, c, f, w0.clone(), 1e-9, nu1, nu2, 20)  # (V(1,1) may need more cycles)
+        w2 = w0.clone()
+        assert S.solve(a, c, f, w2, tol, nu1, nu2, kmax) == want
+        assert torch.equal(w1, w2)
+    bad = f.clone()
+    bad[3, 5] = float("nan")
+    w3 = w0.clone()
+    with pytest.raises(FasError):
+        S.solve(a, c, bad, w3, 1e-9, nu1, nu2, 20)
+    assert torch.equal(w3, w0)  # not finite from the start: no cycle runs
