@@ -7,6 +7,8 @@ namespace fas {
 constexpr int kStripCols = 112;  // columns a 2D march wavefront writes
 constexpr int kMinSegRows = 8;   // shortest 2D march segment (bounds the partial sums)
 
+// Compute units of the current device (queried once per device).
+int device_cus();
 // Whether level l (not the coarsest) runs the fused pre/post kernels.
 bool fused_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable);
 // Number of norm partial sums a fused post launch on level l leaves (one per wave).

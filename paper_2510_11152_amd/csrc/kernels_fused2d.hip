@@ -10,8 +10,6 @@
 
 namespace fas {
 
-namespace {
-
 // Compute units of the current device (queried once per device).
 int device_cus()
 {
@@ -25,6 +23,8 @@ int device_cus()
     }
     return v;
 }
+
+namespace {
 
 // Rows per segment.  Every segment reads H + S + 2 rows beyond its own, so segments
 // should be long; a launch whose waves all fit the device at once has no tail of late

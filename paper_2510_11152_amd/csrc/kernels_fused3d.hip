@@ -2,18 +2,28 @@
 // sweeps (each both colour phases, Appendix B sets 1-4 then 5-8) per pass, fused with the
 // residual and restriction, or with the prolongation correction, or with the residual norm.
 //
-// Geometry.  A 1024-thread block owns an x-y tile of 64 x 32 cells (thread (px, py) holds
-// the cell pair 2px, 2px+1 of row py) and marches along z through a segment of planes,
+// Geometry.  A block owns an x-y tile of 64 columns and 2 TR rows (thread (px, py) holds the
+// cell pair 2px, 2px+1 of rows 2py and 2py+1) and marches along z through a segment of planes,
 // keeping a ring of planes in registers.  x-neighbours come from the adjacent lane by a
-// DPP shift (a wavefront holds two tile rows; the lanes where the shift crosses a row are
-// halo columns), y-neighbours through a double-buffered LDS exchange (one barrier per
-// plane), z-neighbours from the ring.  Phase s = 1 .. S (S = 2 per sweep) updates plane
-// t - s - LAG when plane t arrives; the residual follows on plane t - S - 1 - LAG.  A halo
-// of H cells on each side of the tile and H planes below the segment are recomputed
-// (neighbouring tiles overlap): each phase reaches one cell further, so H = S covers the
-// phases, and a pass that also takes the residual needs S + 1, rounded up to even to keep
-// 2 x 2 x 2 blocks aligned (one sweep: H = 2 or 4; two sweeps: 4 or 6).  Point formulas
+// DPP shift (a wavefront holds two row pairs; the lanes where the shift crosses rows are
+// halo columns), y-neighbours from the thread's other row or through a double-buffered LDS
+// exchange (one barrier per plane), z-neighbours from the ring.  Phase s = 1 .. S (S = 2 per
+// sweep) updates plane t - s - LAG when plane t arrives; the residual follows on plane
+// t - S - 1 - LAG.  A halo of H cells on each side of the tile and H planes below the segment
+// are recomputed (neighbouring tiles overlap): each phase reaches one cell further, so H = S
+// covers the phases, and a pass that also takes the residual needs S + 1, rounded up to even
+// to keep 2 x 2 x 2 blocks aligned (one sweep: H = 2 or 4; two sweeps: 4 or 6).  Point formulas
 // are those of fas_device.h.
+//
+// Why row pairs: which cell of a pair a phase updates depends on the row's parity, so with one
+// row per thread a wave of two neighbouring rows runs both cases for every phase; a pair of
+// rows has one of each, known at compile time, half of its y-neighbours in registers, and the
+// 2 x 2 x 2 blocks of the transfers to itself (no second barrier for the restriction).  The
+// passes are bound by their issue and by the halo (a two-sweep FP64 tile writes 52 x 20 of its
+// 64 x 32 cells), no longer by either alone.  512^3 FP64: pre pass (two sweeps, residual,
+// restriction) 1289-1309 -> 1036-1056 us, post pass with the norm 1237 -> 1073 us; FP32 pre
+// pass 919 -> 647 us; 48 batched periodic 128^3 FP32 1017 / 995 -> 553 / 565 us; 256^3 FP64
+// 239 / 172 -> 147 / 115 us.
 //
 // Modes: 0 = sweep + residual + restriction (u_c = R u, r_c = R r);
 //        1 = correction u += P(u_c - R u) + sweep;  2 = sweep only;
@@ -37,10 +47,17 @@ namespace fas {
 
 namespace {
 
-constexpr int kTPX = 32, kTPY = 32;        // pairs per row, rows per tile
-constexpr int kThreads3 = kTPX * kTPY;     // 1024
+constexpr int kTPX = 32;                   // pairs per row
 constexpr int kWX = 2 * kTPX;              // tile width in cells (64)
-constexpr int kSegPlanes = 64;
+constexpr int kMinSegPlanes = 4;
+
+// Row pairs of a tile.  FP64: 16 (512 threads of 256 VGPRs: the ring of two rows and eight to
+// ten planes takes 128 to 160).  FP32: 24 (768 threads of 168 VGPRs), whose 48-row tile writes
+// 36 rows with two sweeps and the residual, a 32-row tile 20: 512^3 646 against 729 us per
+// pre pass (32 pairs, 1024 threads of 128 VGPRs, spill: 653 us), 20 batched 64^3 47 against
+// 64 us, a single 64^3 level 25 against 22 us.
+template <typename T>
+constexpr int kRows3 = sizeof(T) == 8 ? 16 : 24;
 
 template <typename T>
 struct March3Args {
@@ -123,27 +140,26 @@ constexpr int halo3(int ns, int mode, bool norm)
 
 template <typename T, int NS, int MODE, bool NORM, bool RHS>
 struct Geom3 {
+    static constexpr int TR = kRows3<T>;        // row pairs of the tile
     static constexpr int S = 2 * NS;            // colour phases in the pass
     static constexpr int H = halo3(NS, MODE, NORM);
     static constexpr bool RES = MODE == 0 || MODE == 3 || NORM;  // residual of the final plane
     // the correction (mode 1) and the right-hand side (RHS) need the plane below untouched
     static constexpr int LAG = (MODE == 1 || RHS) ? 1 : 0;
-    // planes loaded ahead: one for two FP64 sweeps, whose ring of planes fills the 128
-    // VGPRs of a 1024-lane block (with two, the FP64 two-sweep passes spill)
-    static constexpr int PF = (NS == 2 && sizeof(T) == 8) ? 1 : 2;
+    static constexpr int PF = 2;                // planes loaded ahead
     static constexpr int RING = (S + 3 + LAG + PF + 1) & ~1;  // planes held: >= S + 3 + LAG + PF, even
-    static constexpr int SLOTS = S + 4;         // LDS exchange slots per buffer
+    static constexpr int THREADS = kTPX * TR;
+    // LDS exchange slots per buffer: per phase the cells that the row pairs above and below
+    // read, both cells of both rows for the residual, and for the right-hand side
+    static constexpr int SLOTS = 2 * S + (RES ? 4 : 0) + (RHS ? 4 : 0);
     static constexpr int UX = kWX - 2 * H;      // cells written per tile in x
-    static constexpr int UY = kTPY - 2 * H;     // rows written per tile
+    static constexpr int UY = 2 * TR - 2 * H;   // rows written per tile
 };
 
-// LDS exchange area: two buffers of S + 4 slots: one per colour phase, residual even and
-// odd, and two for the correction pair sums (mode 1) or the initial values (RHS).  The
-// restriction of mode 0 (which uses neither) takes those last two slots of both buffers;
-// the norm reduction reuses the area after the march.
-template <typename T, int SLOTS>
+// LDS exchange area: two buffers; the norm reduction reuses it after the march.
+template <typename T, int SLOTS, int THREADS>
 struct Xchg {
-    T buf[2][SLOTS][kThreads3];
+    T buf[2][SLOTS][THREADS];
 };
 
 // Per-problem arrays of a batched launch (the kernel arguments stay in place).
@@ -159,76 +175,77 @@ struct Arrays3 {
     double* acc64;
 };
 
-template <typename T, int NS, int MODE, bool NORM, bool RHS, bool EDGE, int FIRST>
+// Where a block stands: inside (no index leaves the domain), over a periodic edge (indices
+// wrap, nothing else differs) or over a wall (cells outside are 0 and stay so, cells at the
+// wall have their own diagonals).
+enum { IN_DOMAIN = 0, AT_WALL = 1, AT_WRAP = 2 };
+
+template <typename T, int NS, int MODE, bool NORM, bool RHS, int PLACE, int FIRST>
 __device__ __forceinline__ void march3(const March3Args<T>& a, const Arrays3<T> A,
-                                       Xchg<T, Geom3<T, NS, MODE, NORM, RHS>::SLOTS>& X, int tx, int ty, int seg,
-                                       double* red)
+                                       Xchg<T, Geom3<T, NS, MODE, NORM, RHS>::SLOTS, kTPX * kRows3<T>>& X, int tx,
+                                       int ty, int seg, double* red)
 {
     using G = Geom3<T, NS, MODE, NORM, RHS>;
     using V = typename Pair3<T>::V;
     static_assert(!RHS || MODE == 2, "the right-hand side is formed by a level's first, sweep-only pass");
-    constexpr int S = G::S, H = G::H, RING = G::RING, PF = G::PF, LAG = G::LAG;
+    constexpr int S = G::S, H = G::H, RING = G::RING, PF = G::PF, LAG = G::LAG, TR = G::TR, NT = G::THREADS;
     const int tid = threadIdx.x;
     const int px = tid % kTPX, py = tid / kTPX;
-    const bool periodic = a.bc == BC_PERIODIC;
+    constexpr bool WALL = PLACE == AT_WALL;
     const int x0 = tx * G::UX, y0 = ty * G::UY;
     const int gxe = x0 - H + 2 * px;
-    const int gy0 = y0 - H + py;
+    const int gy0 = y0 - H + 2 * py;  // the thread's even row
     const int z0 = seg * a.seg_planes;
     const int rA = z0 - H;
     const int zend = min(z0 + a.seg_planes, a.n2);
     const int nsteps = zend - rA + S + 1 + LAG;
-    // x / y position of the pair: wrapped (periodic) or in / out of the domain
+    // x / y position of the 2 x 2 cells: wrapped (periodic) or in / out of the domain (sizes and
+    // origins are even: all four are on one side)
     bool xyin = true;
     int gxl = gxe, gyl = gy0;
-    if constexpr (EDGE) {
-        if (periodic) {
-            gxl = wrap3(gxe, a.n0);
-            gyl = wrap3(gy0, a.n1);
-        } else {
-            xyin = gxe >= 0 && gxe < a.n0 && gy0 >= 0 && gy0 < a.n1;
-            gxl = min(max(gxe, 0), a.n0 - 2);
-            gyl = min(max(gy0, 0), a.n1 - 1);
-        }
+    if constexpr (PLACE == AT_WRAP) {
+        gxl = wrap3(gxe, a.n0);
+        gyl = wrap3(gy0, a.n1);
+    } else if constexpr (WALL) {
+        xyin = gxe >= 0 && gxe < a.n0 && gy0 >= 0 && gy0 < a.n1;
+        gxl = min(max(gxe, 0), a.n0 - 2);
+        gyl = min(max(gy0, 0), a.n1 - 2);
     }
-    const bool own = px >= H / 2 && px < kTPX - H / 2 && py >= H && py < kTPY - H && gxe < a.n0 && gy0 < a.n1;
-    // diagonal data: x and y boundary faces of the even / odd cell (z faces per plane)
+    const bool own = px >= H / 2 && px < kTPX - H / 2 && py >= H / 2 && py < TR - H / 2 && gxe < a.n0 && gy0 < a.n1;
+    // boundary faces across x of the even / odd cell, across y of the even / odd row
     const int dsgn = a.bc == BC_DIRICHLET ? 1 : -1;
-    int bye = 0;
-    if (EDGE && !periodic) bye = (gy0 == 0) + (gy0 == a.n1 - 1);
-    const int be = (EDGE && !periodic) ? (gxe == 0) + bye : 0;
-    const int bo = (EDGE && !periodic) ? (gxe + 2 == a.n0) + bye : 0;
+    const int bx[2] = {WALL && gxe == 0, WALL && gxe + 2 == a.n0};
+    const int by[2] = {WALL && gy0 == 0, WALL && gy0 + 2 == a.n1};
     const T k = a.k;
-    T qe_in = a.q[6], qe_zb = a.q[6], qo_in = a.q[6], qo_zb = a.q[6];
-    T we_in = (T)6, we_zb = (T)6, wo_in = (T)6, wo_zb = (T)6;
-    if constexpr (EDGE) {
-        if (!periodic) {
-            const int ce = 6 + dsgn * be, co = 6 + dsgn * bo;
-            qe_in = pick_q3(a, ce);
-            qe_zb = pick_q3(a, ce + dsgn);
-            qo_in = pick_q3(a, co);
-            qo_zb = pick_q3(a, co + dsgn);
-            we_in = (T)ce;
-            we_zb = (T)(ce + dsgn);
-            wo_in = (T)co;
-            wo_zb = (T)(co + dsgn);
+    // 1 / (1 + k W) of cell (row r, column c) inside and on a z boundary
+    T qin[2][2], qzb[2][2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            qin[r][c] = a.q[6];
+            qzb[r][c] = a.q[6];
+            if constexpr (WALL) {
+                const int W = 6 + dsgn * (bx[c] + by[r]);
+                qin[r][c] = pick_q3(a, W);
+                qzb[r][c] = pick_q3(a, W + dsgn);
+            }
         }
-    }
     const int64_t plane = (int64_t)a.n0 * a.n1;
     const int mc0 = a.n0 >> 1, mc1 = a.n1 >> 1;
     const int64_t cplane = (int64_t)mc0 * mc1;
-    const int ym = py > 0 ? tid - kTPX : tid;              // neighbours in the tile (edge rows
-    const int yp = py < kTPY - 1 ? tid + kTPX : tid;       // read themselves: halo rows)
+    const int ym = py > 0 ? tid - kTPX : tid;          // row pairs below and above (those at the
+    const int yp = py < TR - 1 ? tid + kTPX : tid;     // tile's edge read themselves: halo rows)
 
-    T ue[RING], uo[RING], fe[RING], fo[RING], cr[RING];
-    T su_prev = 0, sr_prev = 0;  // restriction: pair sums of the previous plane
+    T u[RING][2][2], f[RING][2][2], cr[RING];  // [plane][row][column]
+    T su_prev[2] = {0, 0}, sr_prev[2] = {0, 0};  // restriction: pair sums of the previous plane
     double acc = 0.0, facc = 0.0;
 
     auto plane_of = [&](int rho, int& gz) -> bool {
         gz = rA + rho;
-        if constexpr (!EDGE) return true;
+        if constexpr (PLACE == IN_DOMAIN) return true;
         if (gz >= 0 && gz < a.n2) return true;
-        if (periodic) {
+        if constexpr (PLACE == AT_WRAP) {
             gz = wrap3(gz, a.n2);
             return true;
         }
@@ -239,32 +256,48 @@ __device__ __forceinline__ void march3(const March3Args<T>& a, const Arrays3<T> 
         int gz;
         const bool zin = plane_of(rho, gz);
         const int64_t off = (int64_t)gz * plane + (int64_t)gyl * a.n0 + gxl;
-        V zu;
-        if (sizeof(T) == 4 && a.zero_in) {
-            zu.x = (T)0;
-            zu.y = (T)0;
-        } else {
-            zu = *reinterpret_cast<const V*>(A.u_in + off);
+        const bool in = !WALL || (zin && xyin);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            V zu;
+            if (sizeof(T) == 4 && a.zero_in) {
+                zu.x = (T)0;
+                zu.y = (T)0;
+            } else {
+                zu = *reinterpret_cast<const V*>(A.u_in + off + r * a.n0);
+            }
+            const V zf = *reinterpret_cast<const V*>(A.f + off + r * a.n0);
+            u[p][r][0] = in ? zu.x : (T)0;
+            u[p][r][1] = in ? zu.y : (T)0;
+            f[p][r][0] = in ? zf.x : (T)0;
+            f[p][r][1] = in ? zf.y : (T)0;
         }
-        V zf = *reinterpret_cast<const V*>(A.f + off);
-        T c = (T)0;
         if constexpr (MODE == 1) {
-            if (odd) c = A.uc[(int64_t)(gz >> 1) * cplane + (int64_t)(gyl >> 1) * mc0 + (gxl >> 1)];
+            cr[p] = (T)0;
+            if (odd) cr[p] = A.uc[(int64_t)(gz >> 1) * cplane + (int64_t)(gyl >> 1) * mc0 + (gxl >> 1)];
         }
-        if constexpr (EDGE) {
-            const bool in = zin && xyin;
-            zu.x = in ? zu.x : (T)0;
-            zu.y = in ? zu.y : (T)0;
-            zf.x = in ? zf.x : (T)0;
-            zf.y = in ? zf.y : (T)0;
-        }
-        ue[p] = zu.x;
-        uo[p] = zu.y;
-        fe[p] = zf.x;
-        fo[p] = zf.y;
-        cr[p] = c;
     };
-    auto zbound = [&](int gz) -> bool { return EDGE && !periodic && (gz == 0 || gz == a.n2 - 1); };
+    auto zbound = [&](int gz) -> bool { return WALL && (gz == 0 || gz == a.n2 - 1); };
+
+    // Neighbour sum of cell (r, c) of ring plane a0 (planes am below, ap above); yb: the value
+    // across the row pair's edge (below row 0 or above row 1).
+    auto nb_sum = [&](int r, int c, int a0, int am, int ap, T yb) -> T {
+        const T xs = c == 0 ? dpp3<kShr1>(u[a0][r][1]) + u[a0][r][1] : u[a0][r][0] + dpp3<kShl1>(u[a0][r][0]);
+        const T ys = r == 0 ? yb + u[a0][1][c] : u[a0][0][c] + yb;
+        return (xs + ys) + (u[am][r][c] + u[ap][r][c]);
+    };
+    // (A u) of that cell, given its neighbour sum.
+    auto apply = [&](int r, int c, int a0, T Ssum, bool zb) -> T {
+        const T W = (T)(WALL ? 6 + dsgn * (bx[c] + by[r] + (zb ? 1 : 0)) : 6);
+        return u[a0][r][c] + k * (W * u[a0][r][c] - Ssum);
+    };
+    // Both cells of both rows, for the row pairs below (slots 0, 1) and above (slots 2, 3).
+    auto publish4 = [&](T (*B)[NT], int a0) {
+        B[0][tid] = u[a0][0][0];
+        B[1][tid] = u[a0][0][1];
+        B[2][tid] = u[a0][1][0];
+        B[3][tid] = u[a0][1][1];
+    };
 
 #pragma unroll
     for (int p = 0; p < PF; ++p) load_plane(p, p, p & 1);
@@ -279,200 +312,170 @@ __device__ __forceinline__ void march3(const March3Args<T>& a, const Arrays3<T> 
             const int rho = rb + j;
             load_plane(min(rho + PF, nsteps - 1), (j + PF) % RING, ((j + PF) & 1) != 0);
             constexpr int sh = 4 * RING;
-            T* B2 = X.buf[j & 1][S];      // residual: even / odd cells of the final plane
-            T* B3 = X.buf[j & 1][S + 1];
-            T* B4 = X.buf[j & 1][S + 2];  // correction pair sums / initial values (RHS)
-            T* B5 = X.buf[j & 1][S + 3];
-            // publish the values the neighbouring rows read in this step
-            // (colour of a cell: (x + y + z) parity with x, y, z local; all origins even)
+            T(*const B)[NT] = X.buf[j & 1];
+            T(*const BR)[NT] = B + 2 * S;                   // residual
+            T(*const BF)[NT] = B + 2 * S + (G::RES ? 4 : 0);  // right-hand side
+            // publish the values the neighbouring row pairs read in this step (colour of a
+            // cell: (x + y + z) parity with x, y, z local; all origins even): phase s updates
+            // column c of row 0 and column 1 - c of row 1, in every row pair
 #pragma unroll
             for (int s = 1; s <= S; ++s) {
                 const int a0 = (j - s - LAG + sh) % RING;
-                const int colour = ((s - 1) & 1) ^ FIRST;
-                // the other colour's cell of this pair in plane rho - s - LAG
-                const bool other_even = (((py + j - s - LAG + sh) & 1) ^ (1 - colour)) == 0;
-                X.buf[j & 1][s - 1][tid] = other_even ? ue[a0] : uo[a0];
+                const int c = ((j - s - LAG + sh) & 1) ^ ((s - 1) & 1) ^ FIRST;
+                B[2 * s - 2][tid] = u[a0][1][c];      // below row 0 of the pair above
+                B[2 * s - 1][tid] = u[a0][0][1 - c];  // above row 1 of the pair below
             }
-            if constexpr (G::RES) {
-                const int a0 = (j - S - 1 - LAG + sh) % RING;
-                B2[tid] = ue[a0];
-                B3[tid] = uo[a0];
-            }
-            if constexpr (MODE == 1) {
-                if (j & 1) {
-                    const int jp = (j + RING - 1) % RING;
-                    B4[tid] = ue[jp] + uo[jp];  // pair sums along x of planes rho - 1, rho
-                    B5[tid] = ue[j] + uo[j];
-                }
-            }
-            if constexpr (RHS) {
-                const int a0 = (j - LAG + sh) % RING;  // plane rho - 1, initial values
-                B4[tid] = ue[a0];
-                B5[tid] = uo[a0];
-            }
+            if constexpr (G::RES) publish4(BR, (j - S - 1 - LAG + sh) % RING);
+            if constexpr (RHS) publish4(BF, (j - LAG + sh) % RING);  // plane rho - 1, initial values
             __syncthreads();
             if constexpr (RHS) {
                 // FAS right-hand side of plane rho - LAG (f held r)
-                const int r = rho - LAG;
+                const int r3 = rho - LAG;
                 int gz;
-                const bool zin = plane_of(r, gz);
-                if (r >= 1 && (!EDGE || zin)) {
+                const bool zin = plane_of(r3, gz);
+                if (r3 >= 1 && (!WALL || zin)) {
                     const int a0 = (j - LAG + sh) % RING;
                     const int am = (j - LAG - 1 + sh) % RING;
                     const int ap = (j - LAG + 1 + sh) % RING;
-                    const T w = dpp3<kShr1>(uo[a0]);
-                    const T e = dpp3<kShl1>(ue[a0]);
-                    const T Se = ((w + uo[a0]) + (B4[ym] + B4[yp])) + (ue[am] + ue[ap]);
-                    const T So = ((ue[a0] + e) + (B5[ym] + B5[yp])) + (uo[am] + uo[ap]);
                     const bool zb = zbound(gz);
-                    const T We = zb ? we_zb : we_in;
-                    const T Wo = zb ? wo_zb : wo_in;
-                    fe[a0] = fe[a0] + (ue[a0] + k * (We * ue[a0] - Se));
-                    fo[a0] = fo[a0] + (uo[a0] + k * (Wo * uo[a0] - So));
-                    const int graw = rA + r;
-                    if (graw >= z0 && graw < zend && own)
-                        store_pair_nt(A.fout + (int64_t)graw * plane + (int64_t)gy0 * a.n0 + gxe, fe[a0], fo[a0]);
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) {
+                            const T yb = r == 0 ? BF[2 + c][ym] : BF[c][yp];
+                            f[a0][r][c] = f[a0][r][c] + apply(r, c, a0, nb_sum(r, c, a0, am, ap, yb), zb);
+                        }
+                    const int graw = rA + r3;
+                    if (graw >= z0 && graw < zend && own) {
+                        T* const o = A.fout + (int64_t)graw * plane + (int64_t)gy0 * a.n0 + gxe;
+                        store_pair_nt(o, f[a0][0][0], f[a0][0][1]);
+                        store_pair_nt(o + a.n0, f[a0][1][0], f[a0][1][1]);
+                    }
                 }
             }
             if constexpr (MODE == 1) {
-                // fine grid correction on planes (rho - 1, rho) when rho is odd
+                // fine grid correction on planes (rho - 1, rho) when rho is odd: the thread's
+                // cells of the two planes are the children of one coarse cell
                 if (j & 1) {
                     int gz;
                     const bool zin = plane_of(rho, gz);
-                    const int pr = tid ^ kTPX;  // partner row of the coarse cell
-                    const bool even_row = (py & 1) == 0;
-                    const T s00 = even_row ? B4[tid] : B4[pr];  // plane rho-1, rows 2J / 2J+1
-                    const T s10 = even_row ? B4[pr] : B4[tid];
-                    const T s01 = even_row ? B5[tid] : B5[pr];  // plane rho
-                    const T s11 = even_row ? B5[pr] : B5[tid];
+                    const int jp = (j + RING - 1) % RING;
+                    const T s00 = u[jp][0][0] + u[jp][0][1], s10 = u[jp][1][0] + u[jp][1][1];
+                    const T s01 = u[j][0][0] + u[j][0][1], s11 = u[j][1][0] + u[j][1][1];
                     const T old = ((s00 + s10) + (s01 + s11)) * (T)0.125;
                     const T c = cr[j] - old;
-                    const int jp = (j + RING - 1) % RING;
-                    const bool apply = !EDGE || (zin && xyin);
-                    ue[jp] = apply ? ue[jp] + c : ue[jp];
-                    uo[jp] = apply ? uo[jp] + c : uo[jp];
-                    ue[j] = apply ? ue[j] + c : ue[j];
-                    uo[j] = apply ? uo[j] + c : uo[j];
+                    const bool ok = !WALL || (zin && xyin);
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+#pragma unroll
+                        for (int x = 0; x < 2; ++x) {
+                            u[jp][r][x] = ok ? u[jp][r][x] + c : u[jp][r][x];
+                            u[j][r][x] = ok ? u[j][r][x] + c : u[j][r][x];
+                        }
                 }
             }
             // colour phases
 #pragma unroll
             for (int s = 1; s <= S; ++s) {
-                const int r = rho - s - LAG;
-                if (r < 1) continue;
+                const int r3 = rho - s - LAG;
+                if (r3 < 1) continue;
                 int gz;
-                const bool zin = plane_of(r, gz);
-                if (EDGE && !zin) continue;
+                const bool zin = plane_of(r3, gz);
+                if (WALL && !zin) continue;
                 const int a0 = (j - s - LAG + sh) % RING;
                 const int am = (j - s - LAG - 1 + sh) % RING;
                 const int ap = (j - s - LAG + 1 + sh) % RING;
-                const int colour = ((s - 1) & 1) ^ FIRST;
-                const T* Bs = X.buf[j & 1][s - 1];
-                const bool even_cell = (((py + j - s - LAG + sh) & 1) ^ colour) == 0;
+                const int c = ((j - s - LAG + sh) & 1) ^ ((s - 1) & 1) ^ FIRST;
                 const bool zb = zbound(gz);
-                if (even_cell) {
-                    const T w = dpp3<kShr1>(uo[a0]);
-                    const T Ssum = ((w + uo[a0]) + (Bs[ym] + Bs[yp])) + (ue[am] + ue[ap]);
-                    const T qv = zb ? qe_zb : qe_in;
-                    const T nv = (fe[a0] + k * Ssum) * qv;
-                    ue[a0] = (!EDGE || xyin) ? nv : ue[a0];
-                } else {
-                    const T e = dpp3<kShl1>(ue[a0]);
-                    const T Ssum = ((ue[a0] + e) + (Bs[ym] + Bs[yp])) + (uo[am] + uo[ap]);
-                    const T qv = zb ? qo_zb : qo_in;
-                    const T nv = (fo[a0] + k * Ssum) * qv;
-                    uo[a0] = (!EDGE || xyin) ? nv : uo[a0];
-                }
+                const T S0 = nb_sum(0, c, a0, am, ap, B[2 * s - 2][ym]);
+                const T S1 = nb_sum(1, 1 - c, a0, am, ap, B[2 * s - 1][yp]);
+                const T v0 = (f[a0][0][c] + k * S0) * (zb ? qzb[0][c] : qin[0][c]);
+                const T v1 = (f[a0][1][1 - c] + k * S1) * (zb ? qzb[1][1 - c] : qin[1][1 - c]);
+                u[a0][0][c] = (!WALL || xyin) ? v0 : u[a0][0][c];
+                u[a0][1][1 - c] = (!WALL || xyin) ? v1 : u[a0][1][1 - c];
             }
             // plane rho - S - 1 - LAG is final: write, residual, restriction / norm
             {
-                const int r = rho - S - 1 - LAG;
-                if (r >= 1) {
+                const int r3 = rho - S - 1 - LAG;
+                if (r3 >= 1) {
                     int gz;
-                    plane_of(r, gz);
-                    const int graw = rA + r;
+                    plane_of(r3, gz);
+                    const int graw = rA + r3;
                     const bool inseg = graw >= z0 && graw < zend;
                     const int a0 = (j - S - 1 - LAG + sh) % RING;
                     const int am = (j - S - 2 - LAG + sh) % RING;
                     const int ap = (j - S - LAG + sh) % RING;
-                    T re = (T)0, ro = (T)0;
+                    T res[2][2] = {};
                     if constexpr (G::RES) {
-                        const T w = dpp3<kShr1>(uo[a0]);
-                        const T e = dpp3<kShl1>(ue[a0]);
-                        const T Se = ((w + uo[a0]) + (B2[ym] + B2[yp])) + (ue[am] + ue[ap]);
-                        const T So = ((ue[a0] + e) + (B3[ym] + B3[yp])) + (uo[am] + uo[ap]);
                         const bool zb = zbound(gz);
-                        const T We = zb ? we_zb : we_in;
-                        const T Wo = zb ? wo_zb : wo_in;
-                        re = fe[a0] - (ue[a0] + k * (We * ue[a0] - Se));
-                        ro = fo[a0] - (uo[a0] + k * (Wo * uo[a0] - So));
+#pragma unroll
+                        for (int r = 0; r < 2; ++r)
+#pragma unroll
+                            for (int c = 0; c < 2; ++c) {
+                                const T yb = r == 0 ? BR[2 + c][ym] : BR[c][yp];
+                                res[r][c] = f[a0][r][c] - apply(r, c, a0, nb_sum(r, c, a0, am, ap, yb), zb);
+                            }
                     }
                     if (inseg && own) {
-                        const int64_t o = (int64_t)graw * plane + (int64_t)gy0 * a.n0 + gxe;
-                        if constexpr (MODE == 3) {
-                            float2 rv;
-                            rv.x = (float)re;
-                            rv.y = (float)ro;
-                            *reinterpret_cast<float2*>(A.r32 + o) = rv;
-                            if (a.fpartials) {
-                                facc += (double)fe[a0] * (double)fe[a0];
-                                facc += (double)fo[a0] * (double)fo[a0];
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) {
+                            const int64_t o = (int64_t)graw * plane + (int64_t)(gy0 + r) * a.n0 + gxe;
+                            if constexpr (MODE == 3) {
+                                float2 rv;
+                                rv.x = (float)res[r][0];
+                                rv.y = (float)res[r][1];
+                                *reinterpret_cast<float2*>(A.r32 + o) = rv;
+                                if (a.fpartials) {
+                                    facc += (double)f[a0][r][0] * (double)f[a0][r][0];
+                                    facc += (double)f[a0][r][1] * (double)f[a0][r][1];
+                                }
+                            } else if (sizeof(T) == 4 && A.acc64) {
+                                double2* const d = reinterpret_cast<double2*>(A.acc64 + o);
+                                double2 v = *d;
+                                v.x = v.x + (double)u[a0][r][0];
+                                v.y = v.y + (double)u[a0][r][1];
+                                *d = v;
+                            } else {
+                                store_pair_nt(A.u_out + o, u[a0][r][0], u[a0][r][1]);
                             }
-                        } else if (sizeof(T) == 4 && A.acc64) {
-                            double2* const d = reinterpret_cast<double2*>(A.acc64 + o);
-                            double2 v = *d;
-                            v.x = v.x + (double)ue[a0];
-                            v.y = v.y + (double)uo[a0];
-                            *d = v;
-                        } else {
-                            store_pair_nt(A.u_out + o, ue[a0], uo[a0]);
-                        }
-                        if constexpr (NORM) {
-                            acc += (double)re * (double)re;
-                            acc += (double)ro * (double)ro;
+                            if constexpr (NORM) {
+                                acc += (double)res[r][0] * (double)res[r][0];
+                                acc += (double)res[r][1] * (double)res[r][1];
+                            }
                         }
                     }
                     if constexpr (MODE == 0) {
-                        const T su = ue[a0] + uo[a0];
-                        const T sr = re + ro;
+                        const T su[2] = {u[a0][0][0] + u[a0][0][1], u[a0][1][0] + u[a0][1][1]};
+                        const T sr[2] = {res[0][0] + res[0][1], res[1][0] + res[1][1]};
                         // planes (r - 1, r) form coarse plane graw / 2 when r is odd
-                        if (((j - S - 1 - LAG + sh) & 1) && graw - 1 >= z0 && inseg) {
-                            T* R0 = X.buf[0][S + 2];  // slots mode 0 leaves unused
-                            T* R1 = X.buf[0][S + 3];
-                            T* R2 = X.buf[1][S + 2];
-                            T* R3 = X.buf[1][S + 3];
-                            R0[tid] = su_prev;
-                            R1[tid] = sr_prev;
-                            R2[tid] = su;
-                            R3[tid] = sr;
-                            __syncthreads();
-                            const int pr = tid ^ kTPX;
-                            if ((py & 1) == 0 && own) {
-                                // children summed along x (pair), then y (rows), then z
-                                const T ucv = ((R0[tid] + R0[pr]) + (R2[tid] + R2[pr])) * (T)0.125;
-                                const T rcv = ((R1[tid] + R1[pr]) + (R3[tid] + R3[pr])) * (T)0.125;
-                                const int64_t P = (int64_t)(graw >> 1) * cplane + (int64_t)(gy0 >> 1) * mc0 + (gxe >> 1);
-                                __builtin_nontemporal_store(ucv, A.uc + P);
-                                __builtin_nontemporal_store(rcv, A.rc + P);
-                            }
+                        if (((j - S - 1 - LAG + sh) & 1) && graw - 1 >= z0 && inseg && own) {
+                            // children summed along x (pair), then y (rows), then z
+                            const T ucv = ((su_prev[0] + su_prev[1]) + (su[0] + su[1])) * (T)0.125;
+                            const T rcv = ((sr_prev[0] + sr_prev[1]) + (sr[0] + sr[1])) * (T)0.125;
+                            const int64_t P = (int64_t)(graw >> 1) * cplane + (int64_t)(gy0 >> 1) * mc0 + (gxe >> 1);
+                            __builtin_nontemporal_store(ucv, A.uc + P);
+                            __builtin_nontemporal_store(rcv, A.rc + P);
                         }
-                        su_prev = su;
-                        sr_prev = sr;
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) {
+                            su_prev[r] = su[r];
+                            sr_prev[r] = sr[r];
+                        }
                     }
                 }
             }
         }
     }
     if constexpr (NORM) {
-        // red aliases the exchange area; mode 3 sums f^2 beside r^2 in red[kThreads3 ..)
+        // red aliases the exchange area; mode 3 sums f^2 beside r^2 in red[NT ..)
         __syncthreads();
         red[tid] = acc;
-        if constexpr (MODE == 3) red[kThreads3 + tid] = facc;
+        if constexpr (MODE == 3) red[NT + tid] = facc;
         __syncthreads();
-        for (int s = kThreads3 / 2; s > 0; s >>= 1) {
-            if (tid < s) {
+        for (int s = 512; s > 0; s >>= 1) {  // NT <= 1024, not always a power of two
+            if (tid < s && tid + s < NT) {
                 red[tid] = red[tid] + red[tid + s];
-                if constexpr (MODE == 3) red[kThreads3 + tid] = red[kThreads3 + tid] + red[kThreads3 + tid + s];
+                if constexpr (MODE == 3) red[NT + tid] = red[NT + tid] + red[NT + tid + s];
             }
             __syncthreads();
         }
@@ -480,16 +483,17 @@ __device__ __forceinline__ void march3(const March3Args<T>& a, const Arrays3<T> 
 }
 
 template <typename T, int NS, int MODE, bool NORM, bool RHS>
-__global__ __launch_bounds__(kThreads3) void k_march3(March3Args<T> a, int first)
+__global__ __launch_bounds__(kTPX * kRows3<T>) void k_march3(March3Args<T> a, int first)
 {
     using G = Geom3<T, NS, MODE, NORM, RHS>;
-    static_assert(sizeof(Xchg<T, G::SLOTS>) >= (MODE == 3 ? 2 : 1) * kThreads3 * sizeof(double),
+    static_assert(!NORM || sizeof(Xchg<T, G::SLOTS, G::THREADS>) >= (MODE == 3 ? 2 : 1) * G::THREADS * sizeof(double),
                   "norm reductions fit the exchange area");
     static_assert(MODE != 3 || (NS == 0 && NORM && !RHS && sizeof(T) == 8), "mode 3: FP64 residual pass");
-    __shared__ Xchg<T, G::SLOTS> X;
+    __shared__ Xchg<T, G::SLOTS, G::THREADS> X;
     double* red = reinterpret_cast<double*>(&X.buf[0][0][0]);
     // (dispatch order, tile x fastest: the blocks resident at one time cover one z-segment
-    // of neighbouring tiles across all XCDs; an XCD-contiguous renumbering measured slower)
+    // of neighbouring tiles across all XCDs; renumbering so that each XCD takes a contiguous
+    // range of a segment's tiles changed the passes by -4 to +3%, of all tiles by +8 to +14%)
     const int per = a.tiles_x * a.tiles_y * a.segs;
     const int b = blockIdx.x / per, w = blockIdx.x % per;
     if (a.act && !a.act[b]) return;
@@ -505,27 +509,53 @@ __global__ __launch_bounds__(kThreads3) void k_march3(March3Args<T> a, int first
     const int tx = w % a.tiles_x, ty = (w / a.tiles_x) % a.tiles_y, seg = w / (a.tiles_x * a.tiles_y);
     const int x0 = tx * G::UX, y0 = ty * G::UY, z0 = seg * a.seg_planes;
     const int planes_read = a.seg_planes + G::H + G::S + 1 + G::LAG;  // the steps of a full segment
-    const bool edge = x0 - G::H < 0 || x0 - G::H + kWX > a.n0 || y0 - G::H < 0 || y0 - G::H + kTPY > a.n1 ||
+    const bool edge = x0 - G::H < 0 || x0 - G::H + kWX > a.n0 || y0 - G::H < 0 || y0 - G::H + 2 * G::TR > a.n1 ||
                       z0 - G::H < 0 || z0 - G::H + planes_read > a.n2;
-    if (edge) {
-        if (first)
-            march3<T, NS, MODE, NORM, RHS, true, 1>(a, A, X, tx, ty, seg, red);
-        else
-            march3<T, NS, MODE, NORM, RHS, true, 0>(a, A, X, tx, ty, seg, red);
-    } else {
-        if (first)
-            march3<T, NS, MODE, NORM, RHS, false, 1>(a, A, X, tx, ty, seg, red);
-        else
-            march3<T, NS, MODE, NORM, RHS, false, 0>(a, A, X, tx, ty, seg, red);
-    }
+#define FAS_MARCH3(PLACE_)                                                           \
+    do {                                                                             \
+        if (first)                                                                   \
+            march3<T, NS, MODE, NORM, RHS, PLACE_, 1>(a, A, X, tx, ty, seg, red);    \
+        else                                                                         \
+            march3<T, NS, MODE, NORM, RHS, PLACE_, 0>(a, A, X, tx, ty, seg, red);    \
+    } while (0)
+    if (!edge)
+        FAS_MARCH3(IN_DOMAIN);
+    else if (a.bc == BC_PERIODIC)
+        FAS_MARCH3(AT_WRAP);
+    else
+        FAS_MARCH3(AT_WALL);
+#undef FAS_MARCH3
     if constexpr (NORM) {
         if (threadIdx.x == 0) {
             a.partials[(int64_t)b * per + w] = red[0];
             if constexpr (MODE == 3) {
-                if (a.fpartials) a.fpartials[(int64_t)b * per + w] = red[kThreads3];
+                if (a.fpartials) a.fpartials[(int64_t)b * per + w] = red[G::THREADS];
             }
         }
     }
+}
+
+// Planes per segment: a launch takes about (rounds of blocks over the compute units) x (planes
+// of a segment + `extra` planes of halo and lag) steps; the number of segments that makes this
+// least.  With 64-plane segments,
+// halved until there were 512 blocks, 64^3 to 256^3 levels ran up to twice the steps (a launch
+// of 260 blocks on 256 compute units takes two rounds): 256^3 FP64 pre pass 201 -> 147 us,
+// 128^3 60 -> 44 us.
+int segment_planes(int64_t tiles, int n2, int extra)
+{
+    const unsigned cus = (unsigned)device_cus();
+    unsigned best = (unsigned)n2;
+    uint64_t least = ~(uint64_t)0;
+    for (unsigned segs = 1; segs <= (unsigned)n2 / kMinSegPlanes; ++segs) {
+        const unsigned planes = 2 * (((unsigned)n2 + 2 * segs - 1) / (2 * segs));  // even: 2 x 2 x 2 blocks
+        const unsigned n = (unsigned)tiles * (((unsigned)n2 + planes - 1) / planes);
+        const uint64_t steps = (uint64_t)((n + cus - 1) / cus) * (planes + (unsigned)extra);
+        if (steps < least) {
+            least = steps;
+            best = planes;
+        }
+    }
+    return (int)best;
 }
 
 template <typename T>
@@ -540,10 +570,8 @@ March3Args<T> make_args3(const fas_grid* g, int l, const Coef& c, int ns, int mo
     for (int W = 0; W < 16; ++W) a.q[W] = (T)c.q[W];
     const int H = halo3(ns, mode, norm);
     a.tiles_x = (a.n0 + (kWX - 2 * H) - 1) / (kWX - 2 * H);
-    a.tiles_y = (a.n1 + (kTPY - 2 * H) - 1) / (kTPY - 2 * H);
-    a.seg_planes = kSegPlanes;
-    while (a.seg_planes > 8 && (int64_t)g->batch * a.tiles_x * a.tiles_y * ((a.n2 + a.seg_planes - 1) / a.seg_planes) < 512)
-        a.seg_planes >>= 1;
+    a.tiles_y = (a.n1 + (2 * kRows3<T> - 2 * H) - 1) / (2 * kRows3<T> - 2 * H);
+    a.seg_planes = segment_planes((int64_t)g->batch * a.tiles_x * a.tiles_y, a.n2, H + 2 * ns + 2);
     if (g->seg_rows[l]) a.seg_planes = g->seg_rows[l];
     if (g->seg_force) a.seg_planes = g->seg_force < a.n2 ? g->seg_force : a.n2;
     a.segs = (a.n2 + a.seg_planes - 1) / a.seg_planes;
@@ -564,7 +592,7 @@ template <typename T, int NS, int MODE, bool NORM, bool RHS = false>
 void go3(const fas_grid* g, const March3Args<T>& a, int first)
 {
     const unsigned blocks = (unsigned)((int64_t)a.batch * a.tiles_x * a.tiles_y * a.segs);
-    k_march3<T, NS, MODE, NORM, RHS><<<blocks, kThreads3, 0, g->stream>>>(a, first);
+    k_march3<T, NS, MODE, NORM, RHS><<<blocks, kTPX * kRows3<T>, 0, g->stream>>>(a, first);
 }
 
 template <typename T>
@@ -611,8 +639,9 @@ bool fused3_ok(const fas_grid* g, int l, bool variable)
 
 int fused3_partials(const fas_grid* g, int l, int ns)
 {
-    const March3Args<double> a = make_args3<double>(g, l, g->coef[l], ns, 2, true);
-    return a.tiles_x * a.tiles_y * a.segs;
+    auto blocks = [](const auto& a) { return a.tiles_x * a.tiles_y * a.segs; };
+    return g->dtype == FAS_F64 ? blocks(make_args3<double>(g, l, g->coef[l], ns, 2, true))
+                               : blocks(make_args3<float>(g, l, g->coef[l], ns, 2, true));
 }
 
 int launch_march3_resid(const fas_grid* g, const Coef& c, const void* f, const void* u, void* r32, double* partials,
