@@ -56,9 +56,18 @@ bool fused_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable)
     (void)variable;  // constant and cell kappa alike (cell kappa only on single grids)
     if (!g->fused || g->dim != 2 || l >= g->L) return false;
     if (nu_pre > 3 || nu_post > 3) return false;
-    // at least one full strip wide (so a periodic halo wraps at most once) and a few
+    const int n0 = g->lev[l].n[0], n1 = g->lev[l].n[1];
+    // strips: at least one full strip wide (so a periodic halo wraps at most once) and a few
     // rows per segment
-    return g->lev[l].n[0] >= 128 && g->lev[l].n[1] >= 64;
+    if (n0 >= 128 && n1 >= 64) return true;
+    // block tiles also take smaller levels: two launches of 5-7 us in place of the eight
+    // colour phases, two transfers and the right-hand side of the per-level kernels.  The lines
+    // at 32 columns and 8 rows are those down to which they win whatever the other axis, though
+    // a tile computes 128 columns and 32 rows: cycles at 32 x 2^20 cells 1539 -> 834 us (FP64),
+    // 918 -> 491 (FP32), 96 x 65536 310 -> 108 and 220 -> 73, 65536 x 8 55 -> 31 and 54 -> 33,
+    // 112 x 72 34 -> 17; 16 x 2^20 733 -> 729 and 466 -> 401 (periodic 728 -> 766), 8 x 2^20
+    // 369 -> 660, 2^20 x 4 FP32 138 -> 156.
+    return nu_pre >= 1 && nu_post >= 1 && n0 >= 32 && n1 >= 8 && (int64_t)n0 * n1 <= g->tile_max;
 }
 
 int fused_seg_rows(const fas_grid* g, int l, int nu)

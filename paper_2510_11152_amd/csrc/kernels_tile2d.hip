@@ -145,11 +145,10 @@ __device__ __forceinline__ void tile_pass(const TileArgs<T>& a, int b, int t, in
     const int gxe = x0 - kTileHX + 2 * lane;       // even cell of this lane
     const int rb = y0 - H + w * B;                 // row of the wave's first row (even)
     const bool periodic = a.bc == BC_PERIODIC;
-    // A window reaches at most 8 columns / H rows before the domain and less than one
-    // domain size past it (levels are at least 128 x 64), so one wrap step is enough.
+    // (a window may span several periods of a level narrower or lower than it)
     const bool xin = !XE || periodic || (gxe >= 0 && gxe < a.n0);
     const int gxl = !XE ? gxe
-                        : periodic ? gxe + (gxe < 0 ? a.n0 : 0) - (gxe >= a.n0 ? a.n0 : 0)
+                        : periodic ? wrap(gxe, a.n0)
                                    : min(max(gxe, 0), a.n0 - 2);
     const bool own = lane >= kTileHX / 2 && lane < 64 - kTileHX / 2 && (!XE || gxe < a.n0);  // writes this pair
     // boundary faces across x of the even / odd cell (n0 even: a pair is in or out)
@@ -171,7 +170,7 @@ __device__ __forceinline__ void tile_pass(const TileArgs<T>& a, int b, int t, in
     for (int r = 0; r < B; ++r) {
         const int gy = rb + r;
         const bool in = periodic || (gy >= 0 && gy < a.n1);
-        const int gl = periodic ? gy + (gy < 0 ? a.n1 : 0) - (gy >= a.n1 ? a.n1 : 0) : min(max(gy, 0), a.n1 - 1);
+        const int gl = periodic ? wrap(gy, a.n1) : min(max(gy, 0), a.n1 - 1);
         yin[r] = in;
         ys[r] = !periodic && gy == 0;
         yn[r] = !periodic && gy == a.n1 - 1;

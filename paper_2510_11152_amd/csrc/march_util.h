@@ -40,8 +40,8 @@ struct Pair<float> {
 // Index g of a periodic axis of n cells, wrapped into [0, n).
 __device__ __forceinline__ int wrap(int g, int n)
 {
-    int w = g < 0 ? g + n : g - n;
-    if (w < 0 || w >= n) w = ((g % n) + n) % n;
+    int w = g + (g < 0 ? n : 0) - (g >= n ? n : 0);
+    if (w < 0 || w >= n) w = ((g % n) + n) % n;  // more than one period away
     return w;
 }
 
