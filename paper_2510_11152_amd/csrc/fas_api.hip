@@ -361,13 +361,21 @@ std::vector<int> march3_split(const fas_grid* g, int nu, bool form, bool pre)
     return ns;
 }
 
+// Whether level l of a V(pre, post)-cycle runs 3D plane marches.
+bool march3_level(const fas_grid* g, int l, int pre, int post)
+{
+    const bool kv = g->lev[l].kap != nullptr;
+    return fas::fused3_ok(g, l, kv) && pre >= 1 && post >= 1 && !fas::brick_ok(g, l, pre, post, kv);
+}
+
 bool rhs_in_pre(const fas_grid* g, int lc, int pre, int post)
 {
     if (lc < 1 || lc > g->L || !g->lev[lc].r || !g->fused || lc == fas::tail_top(g)) return false;
     const bool kv = g->lev[lc].kap != nullptr;
     // 3D: formed by the first sweep-only pass, so the level needs two pre-sweeps (the
     // sweep-residual-restriction pass has no registers to spare for it)
-    return fas::fused_ok(g, lc, pre, post, kv) || (fas::fused3_ok(g, lc, kv) && pre >= 2 && post >= 1);
+    return fas::fused_ok(g, lc, pre, post, kv) || fas::brick_ok(g, lc, pre, post, kv) ||
+           (march3_level(g, lc, pre, post) && pre >= 2);
 }
 
 // Whether coarse level lc runs its 3D march passes from the level's second buffer: a level
@@ -376,7 +384,7 @@ bool rhs_in_pre(const fas_grid* g, int lc, int pre, int post)
 // iterate in lev[lc].x, so that the last pass ends in lev[lc].u and no copy is needed.
 bool march3_from_x(const fas_grid* g, int lc, int pre, int post)
 {
-    if (!rhs_in_pre(g, lc, pre, post) || !fas::fused3_ok(g, lc, g->lev[lc].kap != nullptr) || post < 1) return false;
+    if (!rhs_in_pre(g, lc, pre, post) || !march3_level(g, lc, pre, post)) return false;
     return (march3_split(g, pre, true, true).size() + march3_split(g, post, false, false).size()) % 2 == 1;
 }
 
@@ -422,7 +430,30 @@ int vcycle_level(fas_grid* g, int l, const void* f, void* u, int pre, int post, 
         fas::launch_tail(g, 0, g->coef, pre, post, first, u, f, false);
         return 0;
     }
-    if (fas::fused3_ok(g, l, g->lev[l].kap != nullptr) && pre >= 1 && post >= 1) {
+    if (fas::brick_ok(g, l, pre, post, g->lev[l].kap != nullptr)) {
+        // small 3D levels: one launch down, one up, u -> second buffer -> u
+        void* const x = g->lev[l].x;
+        void* const ucd = march3_from_x(g, l + 1, pre, post) ? C.x : C.u;
+        const int np = fas::brick_partials(g, l);
+        if (partials && np > g->npartials / g->batch) partials = nullptr;
+        const bool zero = l == 0 && g->zero_start;
+        double* const acc64 = l == 0 ? g->accum64 : nullptr;
+        if (acc64 && partials) throw Error(FAS_ERR_ARG, "internal: accumulation with a norm");
+        {
+            ProfScope ps(g, l, FAS_K_PRE);
+            fas::launch_brick_pre(g, l, g->coef[l], first, pre, rc_in ? rc_in : f, u, x, ucd, rc_dst(g, l, pre, post),
+                                  rc_in ? g->lev[l].f : nullptr, zero);
+            ps.end();
+        }
+        coarse_part(g, l, pre, post, rev);
+        {
+            ProfScope ps(g, l, FAS_K_POST);
+            fas::launch_brick_post(g, l, g->coef[l], first, post, f, x, C.u, u, partials, acc64);
+            ps.end();
+        }
+        return partials ? np : 0;
+    }
+    if (march3_level(g, l, pre, post)) {
         // 3D: passes of up to march3_ns sweeps, ping-pong between u and the level's second
         // buffer; with rc_in the first pass sweeps once, reading it and forming f
         // (= lev[l].f) for the passes after it
@@ -539,16 +570,15 @@ int vcycle_level(fas_grid* g, int l, const void* f, void* u, int pre, int post, 
 bool finest_is_tile(const fas_grid* g, int pre, int post, bool kv)
 {
     if (g->fused && fas::tail_top(g) == 0) return false;
-    if (fas::fused3_ok(g, 0, kv) && pre >= 1 && post >= 1) return false;
     return fas::fused_ok(g, 0, pre, post, kv) && fas::tile_ok(g, 0, pre, post, kv);
 }
 
-// Whether a V(pre, post)-cycle of g runs its finest level as 3D plane-march passes (which
+// Whether a V(pre, post)-cycle of g runs its finest level as 3D plane marches or bricks (which
 // can also start from zero and add their result into an FP64 array).
-bool finest_is_march3(const fas_grid* g, int pre, int post, bool kv)
+bool finest_is_fused3(const fas_grid* g, int pre, int post, bool kv)
 {
     if (g->fused && fas::tail_top(g) == 0) return false;
-    return fas::fused3_ok(g, 0, kv) && pre >= 1 && post >= 1;
+    return (fas::fused3_ok(g, 0, kv) && pre >= 1 && post >= 1) || fas::brick_ok(g, 0, pre, post, kv);
 }
 
 // One cycle on the finest level; with want_norm the squared residual norm of the result
@@ -989,9 +1019,9 @@ int solve_mixed_impl(fas_grid* g64, fas_grid* g32, double dt, double kappa, cons
     g32->active = g64->active;
     g32->gate = 1;
     // the finest FP32 passes start from zero and add into u themselves (tile passes, 3D
-    // plane marches); else the inner iterate is zeroed and added by kernels of their own
+    // plane marches and bricks); else the inner iterate is zeroed and added by kernels of their own
     const bool fold_top = finest_is_tile(g32, nu1, nu2, kcell != nullptr) ||
-                          finest_is_march3(g32, nu1, nu2, kcell != nullptr);
+                          finest_is_fused3(g32, nu1, nu2, kcell != nullptr);
     if (stacked) return solve_mixed_stacked(g64, g32, rhs, u, tol, nu1, nu2, inner, fold_top, status_out, cycles_out);
     char* const span = (char*)g64->rnorm;
     const size_t span_bytes = (size_t)((char*)(g64->hist + fas::kHist) - span);

@@ -84,4 +84,15 @@ void launch_march3(const fas_grid* g, int l, const Coef& c, int first, int mode,
 int launch_march3_resid(const fas_grid* g, const Coef& c, const void* f, const void* u, void* r32, double* partials,
                         double* fpartials);
 
+// Brick passes of small 3D levels (kernels_brick3d.hip): one launch each.  brick_ok: level l
+// takes them, in preference to plane marches.  Arguments as launch_tile_pre / launch_tile_post
+// (acc64 as u64).
+bool brick_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable);
+// Norm partial sums that a post pass leaves per problem.
+int brick_partials(const fas_grid* g, int l);
+void launch_brick_pre(const fas_grid* g, int l, const Coef& c, int first, int nu, const void* f, const void* u_in,
+                      void* u_out, void* uc, void* rc, void* fout, bool zero);
+void launch_brick_post(const fas_grid* g, int l, const Coef& c, int first, int nu, const void* f, const void* u_in,
+                       const void* uc, void* u_out, double* partials, double* acc64);
+
 }  // namespace fas

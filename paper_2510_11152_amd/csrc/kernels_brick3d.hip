@@ -1,0 +1,418 @@
+// Fused 3D passes of small levels (constant kappa) as bricks: a workgroup holds a brick of
+// 8 x 8 x 8 cells with its halo at once (u in LDS, u and f in registers) and runs the pass
+// colour phase by colour phase, one barrier each.  The plane marches (kernels_fused3d.hip)
+// visit a segment's planes one after another, at least (planes + halo) dependent steps, which
+// on a level too small to fill the device is their time: a 64^3 level took two launches of
+// 30 and 26 us a cycle, and a level below the marches' sizes some eleven launches of 5-7 us.
+// A brick pass waits on memory once, then on its phases: V(2,2)-cycles of 64^3 cells
+// 106 -> 52 us (FP64), 95 -> 44 us (FP32), of 32^3 54 -> 30 us, of 48^3 96 -> 38 us.
+//
+// Geometry.  A thread owns a block of 2 x 2 x 2 cells, the children of one coarse cell: half
+// of a cell's neighbours are its registers, the cells that a phase updates are the same for
+// every thread, and the transfers need no neighbour; LDS keeps one plane per cell of the
+// block, indexed by block (as kernels_tail.hip).  A value reaches one cell further along one
+// axis per phase, so a pass reads u within R cells of its brick in the sum of the distances
+// along the axes, not in a cube around it: with two sweeps and the residual (R = 5) 528
+// blocks of the cube's 1000, and f and the phases need fewer still.  The threads are
+// numbered over those blocks only, by a list made at compile time: first the brick's own 64,
+// so that one wave has all of the output work, then the rest in the order of memory (by
+// distance instead: 128^3 FP64 98 -> 80 us for the pre pass; the whole cube: 102 us).
+// A brick still computes eight times what it writes, 15.4 us for a pre pass of 64^3 cells and
+// 80 us at 128^3 (march: 45 us): the price of the short chain, hence only small levels.
+//
+// Passes (Alg. 1): pre = nu sweeps, then u_c = R u and r_c = R (f - A u), on a coarse level
+// forming the FAS right-hand side f = r + A u first; post = u += P (u_c - R u), nu sweeps,
+// optionally one sum of r^2 per brick.  For the inner solves of the mixed form (FP32) a pre
+// pass can start from zero and a post pass add into an FP64 iterate.  Point formulas are those
+// of fas_device.h.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "fas_device.h"
+#include "fas_fused.h"
+#include "fas_internal.h"
+#include "march_util.h"
+
+namespace fas {
+
+namespace {
+
+constexpr int kBrick = 8;            // cells written along each axis
+// Most bricks of a launch on levels that marches take, and on smaller ones (brick_ok).
+constexpr int64_t kBrickMarch = 1536, kBrickMost = 6144;
+
+// Distance (sum over the axes) from a brick up to which a pass reads u: one cell per colour
+// phase, one more for a residual.  f is read one cell less far.
+constexpr int brick_reach(int nu, bool residual) { return 2 * nu + (residual ? 1 : 0); }
+
+// Blocks of 2 x 2 x 2 cells within reach R of a brick: M along each axis of their bounding
+// cube, N of them in all.
+template <int R>
+struct BrickShape {
+    static constexpr int D = (R + 1) / 2, M = kBrick / 2 + 2 * D;
+    static constexpr int out(int i)  // cells between block i of an axis and the brick, plus one (0: inside)
+    {
+        const int d = i < D ? D - i : (i >= D + kBrick / 2 ? i - (D + kBrick / 2) + 1 : 0);
+        return d > 0 ? 2 * d - 1 : 0;
+    }
+    static constexpr int dist(int i, int j, int k) { return out(i) + out(j) + out(k); }
+    static constexpr int count()
+    {
+        int n = 0;
+        for (int k = 0; k < M; ++k)
+            for (int j = 0; j < M; ++j)
+                for (int i = 0; i < M; ++i) n += dist(i, j, k) <= R ? 1 : 0;
+        return n;
+    }
+    static constexpr int N = count(), NT = (N + 63) & ~63;  // threads: one for each block, in whole waves
+};
+
+// The blocks, the brick's own first, the others in the order of memory (i | j << 4 | k << 8 | distance << 12).
+template <int R>
+struct BrickList {
+    unsigned short v[BrickShape<R>::N];
+    constexpr BrickList() : v()
+    {
+        using B = BrickShape<R>;
+        int n = 0;
+        for (int halo = 0; halo <= 1; ++halo)
+            for (int k = 0; k < B::M; ++k)
+                for (int j = 0; j < B::M; ++j)
+                    for (int i = 0; i < B::M; ++i) {
+                        const int d = B::dist(i, j, k);
+                        if (d <= R && (d > 0) == (halo == 1)) v[n++] = (unsigned short)(i | j << 4 | k << 8 | d << 12);
+                    }
+    }
+};
+
+template <typename T>
+struct BrickArgs {
+    int n0, n1, n2;
+    int bc;
+    T k;
+    T q[4];            // 1 / (1 + k W) with 0 .. 3 boundary faces
+    int b0, b1, b2;    // bricks along each axis
+    int64_t stride, cstride;
+    const int* act;
+    const T* f;
+    const T* u_in;
+    T* u_out;
+    T* uc;             // pre: R u out; post: new coarse values in
+    T* rc;             // pre: R r out
+    T* fout;           // pre forming the right-hand side (f then holds r)
+    double* partials;  // post: sum of r^2 per brick
+    int zero_in;       // FP32 pre: u_in is taken as 0 and not read
+    double* acc64;     // FP32 post (nullable): acc64 += fp64(result) in place of storing u_out
+};
+
+// A thread's block of the window; cell c is (c & 1, c >> 1 & 1, c >> 2).
+template <typename T>
+struct BrickBlock {
+    bool on;              // the window has this block
+    bool in;              // it lies in the domain (always, on periodic grids)
+    bool own;             // the brick writes it
+    int o, nb[6];         // LDS index of the block and of its neighbours (0: outside the window)
+    bool lo[3], hi[3];    // the cells at 0 / at 1 along an axis have a boundary face
+    int x, y, z;          // its first cell, inside the domain (wrapped or clamped)
+    T u[8], f[8];
+};
+
+// The pass of one brick; returns the thread's share of the sum of r^2.
+template <typename T, int NU, bool POST, bool RHS, bool NORM>
+__device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, int prob, int bx, int by, int bz, T* lds)
+{
+    constexpr bool RES = !POST || NORM;
+    constexpr int R = brick_reach(NU, RES), D = BrickShape<R>::D, M = BrickShape<R>::M, CAP = M * M * M + 1;
+    static constexpr BrickList<R> list{};
+    static_assert(!(POST && RHS), "a pre pass forms the right-hand side");
+    // a row's cell pair (base pointers need not be aligned to pairs)
+    typedef T V __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+    typedef double V64 __attribute__((ext_vector_type(2), aligned(8)));
+    const bool periodic = a.bc == BC_PERIODIC;
+    const T* const f = a.f + prob * a.stride;
+    const T* const u_in = a.u_in + prob * a.stride;
+    const int n[3] = {a.n0, a.n1, a.n2};
+    const int64_t plane = (int64_t)a.n0 * a.n1;
+    const int mc0 = a.n0 >> 1, mc1 = a.n1 >> 1;
+    auto U = [&](int c) { return lds + c * CAP; };
+    auto row_at = [&](const BrickBlock<T>& B, int c) { return B.x + (int64_t)a.n0 * (B.y + ((c >> 1) & 1)) + plane * (B.z + (c >> 2)); };
+    auto coarse_at = [&](const BrickBlock<T>& B) {
+        return prob * a.cstride + (B.x >> 1) + (int64_t)mc0 * ((B.y >> 1) + (int64_t)mc1 * (B.z >> 1));
+    };
+    // 0 .. 3 boundary faces of cell c -> one of four values
+    auto by_faces = [](const BrickBlock<T>& B, int c, T v0, T v1, T v2, T v3) {
+        const bool x = c & 1 ? B.hi[0] : B.lo[0], y = c & 2 ? B.hi[1] : B.lo[1], z = c & 4 ? B.hi[2] : B.lo[2];
+        const bool all = x && y && z, two = (x && y) || (x && z) || (y && z), any = x || y || z;
+        return all ? v3 : (two ? v2 : (any ? v1 : v0));
+    };
+    auto nb_sum = [&](const BrickBlock<T>& B, int c) {
+        T v[6];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            const int o = c ^ (1 << x);
+            const bool hi = (c >> x) & 1;
+            v[2 * x] = hi ? B.u[o] : U(o)[B.nb[2 * x]];
+            v[2 * x + 1] = hi ? U(o)[B.nb[2 * x + 1]] : B.u[o];
+        }
+        return nbsum<T, 3>(v);
+    };
+    const T d = a.bc == BC_DIRICHLET ? (T)1 : (T)-1;
+    auto apply = [&](const BrickBlock<T>& B, int c) {
+        const T W = by_faces(B, c, (T)6, (T)6 + d, (T)6 + (d + d), (T)6 + (d + d + d));
+        return B.u[c] + a.k * (W * B.u[c] - nb_sum(B, c));
+    };
+
+    // every load is issued before the first use
+    BrickBlock<T> b;
+    T cnew = (T)0;
+    int dist;  // of the block's nearest cell
+    {
+        const int t = (int)threadIdx.x;
+        b.on = t < BrickShape<R>::N;
+        const int code = list.v[b.on ? t : 0];
+        dist = code >> 12;
+        const int pos[3] = {code & 15, code >> 4 & 15, code >> 8 & 15};
+        const int org[3] = {bx * kBrick - 2 * D, by * kBrick - 2 * D, bz * kBrick - 2 * D};
+        const int step[3] = {1, M, M * M};
+        int g[3];
+        b.o = 1 + pos[0] + M * (pos[1] + M * pos[2]);
+        b.in = b.on;
+        b.own = b.on && dist == 0;
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            g[x] = org[x] + 2 * pos[x];
+            b.nb[2 * x] = pos[x] > 0 ? b.o - step[x] : 0;
+            b.nb[2 * x + 1] = pos[x] < M - 1 ? b.o + step[x] : 0;
+            b.own = b.own && g[x] < n[x];
+            b.lo[x] = !periodic && g[x] == 0;
+            b.hi[x] = !periodic && g[x] + 2 == n[x];
+            if (periodic) {  // sizes and origins are even: a block never straddles the edge
+                g[x] = wrap(g[x], n[x]);
+            } else {
+                b.in = b.in && g[x] >= 0 && g[x] < n[x];
+                g[x] = min(max(g[x], 0), n[x] - 2);
+            }
+        }
+        b.x = g[0], b.y = g[1], b.z = g[2];
+#pragma unroll
+        for (int c = 0; c < 8; c += 2) {
+            const int64_t p = row_at(b, c);
+            V vu = {(T)0, (T)0}, vf = {(T)0, (T)0};
+            if (dist < R) vf = *reinterpret_cast<const V*>(f + p);
+            if (!(sizeof(T) == 4 && a.zero_in)) vu = *reinterpret_cast<const V*>(u_in + p);
+            b.u[c] = b.in ? vu.x : (T)0;
+            b.u[c + 1] = b.in ? vu.y : (T)0;
+            b.f[c] = b.in ? vf.x : (T)0;
+            b.f[c + 1] = b.in ? vf.y : (T)0;
+        }
+        if constexpr (POST) cnew = a.uc[coarse_at(b)];
+    }
+    if (threadIdx.x < 8) U((int)threadIdx.x)[0] = (T)0;
+    if constexpr (POST) {
+        // the fine grid correction: the block's cells are the children of one coarse cell
+        const T c = cnew - restrict8(b.u[0], b.u[1], b.u[2], b.u[3], b.u[4], b.u[5], b.u[6], b.u[7]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b.u[i] = b.in ? b.u[i] + c : b.u[i];
+    }
+    if (b.on) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) U(c)[b.o] = b.u[c];
+    }
+    __syncthreads();
+    if constexpr (RHS) {
+        // FAS right-hand side from the initial values: f = r + A u
+#pragma unroll
+        for (int c = 0; c < 8; ++c) b.f[c] = b.f[c] + apply(b, c);
+        if (b.own) {
+#pragma unroll
+            for (int c = 0; c < 8; c += 2) *reinterpret_cast<V*>(a.fout + prob * a.stride + row_at(b, c)) = V{b.f[c], b.f[c + 1]};
+        }
+        __syncthreads();
+    }
+    // colour phases
+    auto phase = [&](auto step, auto par) {
+        constexpr int s = decltype(step)::value, P = decltype(par)::value;
+        // blocks outside the domain stay 0; from this far off no value reaches a result any more
+        if (!b.in || dist > R - 1 - s) return;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            if ((((c & 1) + ((c >> 1) & 1) + (c >> 2)) & 1) != P) continue;
+            b.u[c] = (b.f[c] + a.k * nb_sum(b, c)) * by_faces(b, c, a.q[0], a.q[1], a.q[2], a.q[3]);
+            U(c)[b.o] = b.u[c];
+        }
+    };
+    auto colour = [&](auto step) {
+        if (((decltype(step)::value & 1) ^ first) != 0)
+            phase(step, std::integral_constant<int, 1>{});
+        else
+            phase(step, std::integral_constant<int, 0>{});
+        __syncthreads();
+    };
+    colour(std::integral_constant<int, 0>{});
+    colour(std::integral_constant<int, 1>{});
+    if constexpr (NU == 2) {
+        colour(std::integral_constant<int, 2>{});
+        colour(std::integral_constant<int, 3>{});
+    }
+    double acc = 0.0;
+    if (b.own) {
+#pragma unroll
+        for (int c = 0; c < 8; c += 2) {
+            const int64_t p = prob * a.stride + row_at(b, c);
+            if (POST && sizeof(T) == 4 && a.acc64) {
+                V64* const q = reinterpret_cast<V64*>(a.acc64 + p);
+                const V64 v = *q;
+                *q = V64{v.x + (double)b.u[c], v.y + (double)b.u[c + 1]};
+            } else {
+                *reinterpret_cast<V*>(a.u_out + p) = V{b.u[c], b.u[c + 1]};
+            }
+        }
+        if constexpr (RES) {
+            T r[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) r[c] = b.f[c] - apply(b, c);
+            if constexpr (POST) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) acc += (double)r[c] * (double)r[c];
+            } else {
+                const int64_t P = coarse_at(b);
+                a.uc[P] = restrict8(b.u[0], b.u[1], b.u[2], b.u[3], b.u[4], b.u[5], b.u[6], b.u[7]);
+                a.rc[P] = restrict8(r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7]);
+            }
+        }
+    }
+    return acc;
+}
+
+template <typename T, int NU, bool POST, bool RHS, bool NORM>
+__global__ __launch_bounds__(BrickShape<brick_reach(NU, !POST || NORM)>::NT) void k_brick(BrickArgs<T> a, int first)
+{
+    using B = BrickShape<brick_reach(NU, !POST || NORM)>;
+    __shared__ T lds[8 * (B::M * B::M * B::M + 1)];
+    const int per = a.b0 * a.b1 * a.b2;
+    const int prob = blockIdx.x / per, w = blockIdx.x % per;
+    if (a.act && !a.act[prob]) return;
+    const int bx = w % a.b0, by = (w / a.b0) % a.b1, bz = w / (a.b0 * a.b1);
+    const double acc = brick_pass<T, NU, POST, RHS, NORM>(a, first, prob, bx, by, bz, lds);
+    if constexpr (NORM) {
+        // the brick's own blocks are the first wave's: a fixed butterfly over its lanes
+        double v = acc;
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if (threadIdx.x == 0) a.partials[(int64_t)prob * per + w] = v;
+    }
+}
+
+inline void check_launch()
+{
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) throw Error(FAS_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
+}
+
+template <typename T>
+BrickArgs<T> make_brick_args(const fas_grid* g, int l, const Coef& c)
+{
+    BrickArgs<T> a{};
+    a.n0 = g->lev[l].n[0];
+    a.n1 = g->lev[l].n[1];
+    a.n2 = g->lev[l].n[2];
+    a.bc = g->bc;
+    a.k = (T)c.kd;
+    for (int no = 0; no < 4; ++no) a.q[no] = (T)c.q[diag_count(g->bc, 3, no)];
+    a.b0 = (a.n0 + kBrick - 1) / kBrick;
+    a.b1 = (a.n1 + kBrick - 1) / kBrick;
+    a.b2 = (a.n2 + kBrick - 1) / kBrick;
+    a.stride = g->lev[l].N;
+    a.cstride = g->lev[l + 1].N;
+    a.act = active_flags(g);
+    return a;
+}
+
+template <typename T, bool POST, bool RHS, bool NORM>
+void launch_brick(const fas_grid* g, const BrickArgs<T>& a, int nu, int first)
+{
+    const unsigned blocks = (unsigned)((int64_t)g->batch * a.b0 * a.b1 * a.b2);
+    constexpr bool RES = !POST || NORM;
+    if (nu == 1)
+        k_brick<T, 1, POST, RHS, NORM><<<blocks, BrickShape<brick_reach(1, RES)>::NT, 0, g->stream>>>(a, first);
+    else if (nu == 2)
+        k_brick<T, 2, POST, RHS, NORM><<<blocks, BrickShape<brick_reach(2, RES)>::NT, 0, g->stream>>>(a, first);
+    else
+        throw Error(FAS_ERR_ARG, "internal: brick passes take one or two sweeps");
+    check_launch();
+}
+
+template <typename T>
+void brick_pre(const fas_grid* g, int l, const Coef& c, int first, int nu, const void* f, const void* u_in, void* u_out,
+               void* uc, void* rc, void* fout, bool zero)
+{
+    BrickArgs<T> a = make_brick_args<T>(g, l, c);
+    a.f = (const T*)f, a.u_in = (const T*)u_in, a.u_out = (T*)u_out;
+    a.uc = (T*)uc, a.rc = (T*)rc, a.fout = (T*)fout, a.zero_in = zero ? 1 : 0;
+    if (fout)
+        launch_brick<T, false, true, false>(g, a, nu, first);
+    else
+        launch_brick<T, false, false, false>(g, a, nu, first);
+}
+
+template <typename T>
+void brick_post(const fas_grid* g, int l, const Coef& c, int first, int nu, const void* f, const void* u_in,
+                const void* uc, void* u_out, double* partials, double* acc64)
+{
+    BrickArgs<T> a = make_brick_args<T>(g, l, c);
+    a.f = (const T*)f, a.u_in = (const T*)u_in, a.u_out = (T*)u_out;
+    a.uc = (T*)const_cast<void*>(uc), a.partials = partials, a.acc64 = acc64;
+    if (partials)
+        launch_brick<T, true, false, true>(g, a, nu, first);
+    else
+        launch_brick<T, true, false, false>(g, a, nu, first);
+}
+
+int64_t brick_blocks(const fas_grid* g, int l)
+{
+    int64_t n = 1;
+    for (int a = 0; a < 3; ++a) n *= (g->lev[l].n[a] + kBrick - 1) / kBrick;
+    return n;
+}
+
+}  // namespace
+
+bool brick_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable)
+{
+    if (!g->fused || g->dim != 3 || variable || l >= g->L) return false;
+    if (nu_pre < 1 || nu_pre > 2 || nu_post < 1 || nu_post > 2) return false;
+    const int64_t blocks = g->batch * brick_blocks(g, l);
+    // Where marches could run, pre + post pass (us, march against bricks): 512 bricks (64^3)
+    // 56 -> 27 FP64 and 49 -> 22 FP32, 1024 (two 64^3 with norms) 63 -> 50 and 54 -> 42, 1728
+    // (96^3) 62 -> 62 and 52 -> 47, 2048 (128 x 128 x 64) 58 -> 68 and 52 -> 52.  On levels
+    // below the marches' sizes, whole cycles against the per-level kernels: 6144 bricks
+    // (96 problems of 32^3) 306 -> 282 and 222 -> 184 us, 8192 (8 x 8 x 65536) 213 -> 221 and
+    // 152 -> 153, 16384 (256 of 32^3) 651 -> 660 and 419 -> 405.
+    return blocks <= (fused3_ok(g, l, variable) ? kBrickMarch : kBrickMost);
+}
+
+int brick_partials(const fas_grid* g, int l) { return (int)brick_blocks(g, l); }
+
+void launch_brick_pre(const fas_grid* g, int l, const Coef& c, int first, int nu, const void* f, const void* u_in,
+                      void* u_out, void* uc, void* rc, void* fout, bool zero)
+{
+    if (zero && (fout || g->dtype != FAS_F32))
+        throw Error(FAS_ERR_ARG, "internal: a zero-start pre pass is an FP32 pass that forms nothing else");
+    if (g->dtype == FAS_F64)
+        brick_pre<double>(g, l, c, first, nu, f, u_in, u_out, uc, rc, fout, zero);
+    else
+        brick_pre<float>(g, l, c, first, nu, f, u_in, u_out, uc, rc, fout, zero);
+}
+
+void launch_brick_post(const fas_grid* g, int l, const Coef& c, int first, int nu, const void* f, const void* u_in,
+                       const void* uc, void* u_out, double* partials, double* acc64)
+{
+    if (acc64 && (partials || g->dtype != FAS_F32))
+        throw Error(FAS_ERR_ARG, "internal: the accumulating post pass is an FP32 pass without a norm");
+    if (g->dtype == FAS_F64)
+        brick_post<double>(g, l, c, first, nu, f, u_in, uc, u_out, partials, acc64);
+    else
+        brick_post<float>(g, l, c, first, nu, f, u_in, uc, u_out, partials, acc64);
+}
+
+}  // namespace fas
