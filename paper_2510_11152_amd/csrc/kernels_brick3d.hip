@@ -5,7 +5,7 @@
 // on a level too small to fill the device is their time: a 64^3 level took two launches of
 // 30 and 26 us a cycle, and a level below the marches' sizes some eleven launches of 5-7 us.
 // A brick pass waits on memory once, then on its phases: V(2,2)-cycles of 64^3 cells
-// 106 -> 52 us (FP64), 95 -> 44 us (FP32), of 32^3 54 -> 30 us, of 48^3 96 -> 38 us.
+// 106 -> 49 us (FP64), 95 -> 40 us (FP32), of 32^3 54 -> 29 us, of 48^3 96 -> 37 us.
 //
 // Geometry.  A thread owns a block of 2 x 2 x 2 cells, the children of one coarse cell: half
 // of a cell's neighbours are its registers, the cells that a phase updates are the same for
@@ -16,9 +16,12 @@
 // blocks of the cube's 1000, and f and the phases need fewer still.  The threads are
 // numbered over those blocks only, by a list made at compile time: first the brick's own 64,
 // so that one wave has all of the output work, then the rest in the order of memory (by
-// distance instead: 128^3 FP64 98 -> 80 us for the pre pass; the whole cube: 102 us).
-// A brick still computes eight times what it writes, 15.4 us for a pre pass of 64^3 cells and
-// 80 us at 128^3 (march: 45 us): the price of the short chain, hence only small levels.
+// distance instead: 128^3 FP64 98 -> 80 us for the pre pass; the whole cube: 102 us).  Waves
+// without a boundary face take phases without the selection of their coefficients, and
+// neighbours lie at constant LDS offsets (80 -> 76 us); neighbouring bricks run under one L2
+// (76 -> 71 us, the post pass 41 -> 37, 48 problems of 32^3 68 -> 55).  A brick still computes
+// eight times what it writes, 14 us for a pre pass of 64^3 cells and 71 us at 128^3 (march:
+// 45 us): the price of the short chain, hence only small levels.
 //
 // Passes (Alg. 1): pre = nu sweeps, then u_c = R u and r_c = R (f - A u), on a coarse level
 // forming the FAS right-hand side f = r + A u first; post = u += P (u_c - R u), nu sweeps,
@@ -39,8 +42,8 @@ namespace fas {
 namespace {
 
 constexpr int kBrick = 8;            // cells written along each axis
-// Most bricks of a launch on levels that marches take, and on smaller ones (brick_ok).
-constexpr int64_t kBrickMarch = 1536, kBrickMost = 6144;
+// Most bricks of a launch on levels that marches take (FP64, FP32), and on smaller ones (brick_ok).
+constexpr int64_t kBrickMarch64 = 1536, kBrickMarch32 = 2048, kBrickMost = 8192;
 
 // Distance (sum over the axes) from a brick up to which a pass reads u: one cell per colour
 // phase, one more for a residual.  f is read one cell less far.
@@ -66,6 +69,9 @@ struct BrickShape {
         return n;
     }
     static constexpr int N = count(), NT = (N + 63) & ~63;  // threads: one for each block, in whole waves
+    // LDS indices of a plane of cells; with R even the outermost blocks are updated in part, and
+    // what their outer cells would read lies in the padding
+    static constexpr int PAD = R % 2 ? 0 : M * M, CAP = M * M * M + 2 * PAD;
 };
 
 // The blocks, the brick's own first, the others in the order of memory (i | j << 4 | k << 8 | distance << 12).
@@ -112,9 +118,10 @@ struct BrickBlock {
     bool on;              // the window has this block
     bool in;              // it lies in the domain (always, on periodic grids)
     bool own;             // the brick writes it
-    int o, nb[6];         // LDS index of the block and of its neighbours (0: outside the window)
+    int o;                // LDS index of the block
     bool lo[3], hi[3];    // the cells at 0 / at 1 along an axis have a boundary face
-    int x, y, z;          // its first cell, inside the domain (wrapped or clamped)
+    unsigned row[4];      // byte offsets of its cell pairs in the domain (wrapped or clamped)
+    unsigned coarse;      // and of its coarse cell
     T u[8], f[8];
 };
 
@@ -123,25 +130,25 @@ template <typename T, int NU, bool POST, bool RHS, bool NORM>
 __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, int prob, int bx, int by, int bz, T* lds)
 {
     constexpr bool RES = !POST || NORM;
-    constexpr int R = brick_reach(NU, RES), D = BrickShape<R>::D, M = BrickShape<R>::M, CAP = M * M * M + 1;
+    constexpr int R = brick_reach(NU, RES), D = BrickShape<R>::D, M = BrickShape<R>::M, CAP = BrickShape<R>::CAP;
     static constexpr BrickList<R> list{};
     static_assert(!(POST && RHS), "a pre pass forms the right-hand side");
     // a row's cell pair (base pointers need not be aligned to pairs)
     typedef T V __attribute__((ext_vector_type(2), aligned(sizeof(T))));
     typedef double V64 __attribute__((ext_vector_type(2), aligned(8)));
     const bool periodic = a.bc == BC_PERIODIC;
-    const T* const f = a.f + prob * a.stride;
-    const T* const u_in = a.u_in + prob * a.stride;
     const int n[3] = {a.n0, a.n1, a.n2};
-    const int64_t plane = (int64_t)a.n0 * a.n1;
-    const int mc0 = a.n0 >> 1, mc1 = a.n1 >> 1;
     auto U = [&](int c) { return lds + c * CAP; };
-    auto row_at = [&](const BrickBlock<T>& B, int c) { return B.x + (int64_t)a.n0 * (B.y + ((c >> 1) & 1)) + plane * (B.z + (c >> 2)); };
-    auto coarse_at = [&](const BrickBlock<T>& B) {
-        return prob * a.cstride + (B.x >> 1) + (int64_t)mc0 * ((B.y >> 1) + (int64_t)mc1 * (B.z >> 1));
+    // cell pairs and coarse values of this problem's arrays by byte offset
+    auto pair_at = [&](const T* v, unsigned byte) {
+        return reinterpret_cast<V*>(reinterpret_cast<char*>(const_cast<T*>(v + prob * a.stride)) + byte);
+    };
+    auto coarse_at = [&](T* v, unsigned byte) {
+        return reinterpret_cast<T*>(reinterpret_cast<char*>(v + prob * a.cstride) + byte);
     };
     // 0 .. 3 boundary faces of cell c -> one of four values
-    auto by_faces = [](const BrickBlock<T>& B, int c, T v0, T v1, T v2, T v3) {
+    auto by_faces = [](auto walls, const BrickBlock<T>& B, int c, T v0, T v1, T v2, T v3) {
+        if (!decltype(walls)::value) return v0;
         const bool x = c & 1 ? B.hi[0] : B.lo[0], y = c & 2 ? B.hi[1] : B.lo[1], z = c & 4 ? B.hi[2] : B.lo[2];
         const bool all = x && y && z, two = (x && y) || (x && z) || (y && z), any = x || y || z;
         return all ? v3 : (two ? v2 : (any ? v1 : v0));
@@ -152,14 +159,15 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
         for (int x = 0; x < 3; ++x) {
             const int o = c ^ (1 << x);
             const bool hi = (c >> x) & 1;
-            v[2 * x] = hi ? B.u[o] : U(o)[B.nb[2 * x]];
-            v[2 * x + 1] = hi ? U(o)[B.nb[2 * x + 1]] : B.u[o];
+            constexpr int step[3] = {1, M, M * M};
+            v[2 * x] = hi ? B.u[o] : U(o)[B.o - step[x]];
+            v[2 * x + 1] = hi ? U(o)[B.o + step[x]] : B.u[o];
         }
         return nbsum<T, 3>(v);
     };
     const T d = a.bc == BC_DIRICHLET ? (T)1 : (T)-1;
-    auto apply = [&](const BrickBlock<T>& B, int c) {
-        const T W = by_faces(B, c, (T)6, (T)6 + d, (T)6 + (d + d), (T)6 + (d + d + d));
+    auto apply = [&](auto walls, const BrickBlock<T>& B, int c) {
+        const T W = by_faces(walls, B, c, (T)6, (T)6 + d, (T)6 + (d + d), (T)6 + (d + d + d));
         return B.u[c] + a.k * (W * B.u[c] - nb_sum(B, c));
     };
 
@@ -174,16 +182,13 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
         dist = code >> 12;
         const int pos[3] = {code & 15, code >> 4 & 15, code >> 8 & 15};
         const int org[3] = {bx * kBrick - 2 * D, by * kBrick - 2 * D, bz * kBrick - 2 * D};
-        const int step[3] = {1, M, M * M};
         int g[3];
-        b.o = 1 + pos[0] + M * (pos[1] + M * pos[2]);
+        b.o = BrickShape<R>::PAD + pos[0] + M * (pos[1] + M * pos[2]);
         b.in = b.on;
         b.own = b.on && dist == 0;
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
             g[x] = org[x] + 2 * pos[x];
-            b.nb[2 * x] = pos[x] > 0 ? b.o - step[x] : 0;
-            b.nb[2 * x + 1] = pos[x] < M - 1 ? b.o + step[x] : 0;
             b.own = b.own && g[x] < n[x];
             b.lo[x] = !periodic && g[x] == 0;
             b.hi[x] = !periodic && g[x] + 2 == n[x];
@@ -194,21 +199,29 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
                 g[x] = min(max(g[x], 0), n[x] - 2);
             }
         }
-        b.x = g[0], b.y = g[1], b.z = g[2];
+        const unsigned first_cell = g[0] + (unsigned)a.n0 * (g[1] + (unsigned)a.n1 * g[2]);
+        b.coarse = (g[0] / 2 + (unsigned)(a.n0 / 2) * (g[1] / 2 + (unsigned)(a.n1 / 2) * (g[2] / 2))) * sizeof(T);
 #pragma unroll
-        for (int c = 0; c < 8; c += 2) {
-            const int64_t p = row_at(b, c);
+        for (int i = 0; i < 4; ++i) {
+            b.row[i] = (first_cell + (i & 1) * (unsigned)a.n0 + (i >> 1) * (unsigned)(a.n0 * a.n1)) * sizeof(T);
             V vu = {(T)0, (T)0}, vf = {(T)0, (T)0};
-            if (dist < R) vf = *reinterpret_cast<const V*>(f + p);
-            if (!(sizeof(T) == 4 && a.zero_in)) vu = *reinterpret_cast<const V*>(u_in + p);
-            b.u[c] = b.in ? vu.x : (T)0;
-            b.u[c + 1] = b.in ? vu.y : (T)0;
-            b.f[c] = b.in ? vf.x : (T)0;
-            b.f[c + 1] = b.in ? vf.y : (T)0;
+            if (b.in && dist < R) vf = *pair_at(a.f, b.row[i]);
+            if (b.in && !(sizeof(T) == 4 && a.zero_in)) vu = *pair_at(a.u_in, b.row[i]);
+            b.u[2 * i] = vu.x;
+            b.u[2 * i + 1] = vu.y;
+            b.f[2 * i] = vf.x;
+            b.f[2 * i + 1] = vf.y;
         }
-        if constexpr (POST) cnew = a.uc[coarse_at(b)];
+        if constexpr (POST) cnew = *coarse_at(a.uc, b.coarse);
     }
-    if (threadIdx.x < 8) U((int)threadIdx.x)[0] = (T)0;
+    // whether any block of the wave has a boundary face
+    const bool walls = __any(b.lo[0] || b.hi[0] || b.lo[1] || b.hi[1] || b.lo[2] || b.hi[2]) != 0;
+    auto with_walls = [&](auto&& body) {
+        if (walls)
+            body(std::true_type{});
+        else
+            body(std::false_type{});
+    };
     if constexpr (POST) {
         // the fine grid correction: the block's cells are the children of one coarse cell
         const T c = cnew - restrict8(b.u[0], b.u[1], b.u[2], b.u[3], b.u[4], b.u[5], b.u[6], b.u[7]);
@@ -222,31 +235,36 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
     __syncthreads();
     if constexpr (RHS) {
         // FAS right-hand side from the initial values: f = r + A u
+        with_walls([&](auto wl) {
+            if (dist >= R) return;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) b.f[c] = b.f[c] + apply(b, c);
+            for (int c = 0; c < 8; ++c) b.f[c] = b.f[c] + apply(wl, b, c);
+        });
         if (b.own) {
 #pragma unroll
-            for (int c = 0; c < 8; c += 2) *reinterpret_cast<V*>(a.fout + prob * a.stride + row_at(b, c)) = V{b.f[c], b.f[c + 1]};
+            for (int i = 0; i < 4; ++i) *pair_at(a.fout, b.row[i]) = V{b.f[2 * i], b.f[2 * i + 1]};
         }
         __syncthreads();
     }
     // colour phases
-    auto phase = [&](auto step, auto par) {
+    auto phase = [&](auto step, auto par, auto wl) {
         constexpr int s = decltype(step)::value, P = decltype(par)::value;
         // blocks outside the domain stay 0; from this far off no value reaches a result any more
         if (!b.in || dist > R - 1 - s) return;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             if ((((c & 1) + ((c >> 1) & 1) + (c >> 2)) & 1) != P) continue;
-            b.u[c] = (b.f[c] + a.k * nb_sum(b, c)) * by_faces(b, c, a.q[0], a.q[1], a.q[2], a.q[3]);
+            b.u[c] = (b.f[c] + a.k * nb_sum(b, c)) * by_faces(wl, b, c, a.q[0], a.q[1], a.q[2], a.q[3]);
             U(c)[b.o] = b.u[c];
         }
     };
     auto colour = [&](auto step) {
-        if (((decltype(step)::value & 1) ^ first) != 0)
-            phase(step, std::integral_constant<int, 1>{});
-        else
-            phase(step, std::integral_constant<int, 0>{});
+        with_walls([&](auto wl) {
+            if (((decltype(step)::value & 1) ^ first) != 0)
+                phase(step, std::integral_constant<int, 1>{}, wl);
+            else
+                phase(step, std::integral_constant<int, 0>{}, wl);
+        });
         __syncthreads();
     };
     colour(std::integral_constant<int, 0>{});
@@ -258,27 +276,27 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
     double acc = 0.0;
     if (b.own) {
 #pragma unroll
-        for (int c = 0; c < 8; c += 2) {
-            const int64_t p = prob * a.stride + row_at(b, c);
+        for (int i = 0; i < 4; ++i) {
             if (POST && sizeof(T) == 4 && a.acc64) {
-                V64* const q = reinterpret_cast<V64*>(a.acc64 + p);
+                V64* const q = reinterpret_cast<V64*>(reinterpret_cast<char*>(a.acc64 + prob * a.stride) + 2 * (size_t)b.row[i]);
                 const V64 v = *q;
-                *q = V64{v.x + (double)b.u[c], v.y + (double)b.u[c + 1]};
+                *q = V64{v.x + (double)b.u[2 * i], v.y + (double)b.u[2 * i + 1]};
             } else {
-                *reinterpret_cast<V*>(a.u_out + p) = V{b.u[c], b.u[c + 1]};
+                *pair_at(a.u_out, b.row[i]) = V{b.u[2 * i], b.u[2 * i + 1]};
             }
         }
         if constexpr (RES) {
             T r[8];
+            with_walls([&](auto wl) {
 #pragma unroll
-            for (int c = 0; c < 8; ++c) r[c] = b.f[c] - apply(b, c);
+                for (int c = 0; c < 8; ++c) r[c] = b.f[c] - apply(wl, b, c);
+            });
             if constexpr (POST) {
 #pragma unroll
                 for (int c = 0; c < 8; ++c) acc += (double)r[c] * (double)r[c];
             } else {
-                const int64_t P = coarse_at(b);
-                a.uc[P] = restrict8(b.u[0], b.u[1], b.u[2], b.u[3], b.u[4], b.u[5], b.u[6], b.u[7]);
-                a.rc[P] = restrict8(r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7]);
+                *coarse_at(a.uc, b.coarse) = restrict8(b.u[0], b.u[1], b.u[2], b.u[3], b.u[4], b.u[5], b.u[6], b.u[7]);
+                *coarse_at(a.rc, b.coarse) = restrict8(r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7]);
             }
         }
     }
@@ -289,9 +307,13 @@ template <typename T, int NU, bool POST, bool RHS, bool NORM>
 __global__ __launch_bounds__(BrickShape<brick_reach(NU, !POST || NORM)>::NT) void k_brick(BrickArgs<T> a, int first)
 {
     using B = BrickShape<brick_reach(NU, !POST || NORM)>;
-    __shared__ T lds[8 * (B::M * B::M * B::M + 1)];
+    __shared__ T lds[8 * B::CAP];
     const int per = a.b0 * a.b1 * a.b2;
-    const int prob = blockIdx.x / per, w = blockIdx.x % per;
+    // neighbouring bricks share most of what they read: each of the 8 L2 caches (blocks go to
+    // them in turn) gets a contiguous eighth of the bricks
+    const int share = gridDim.x / 8, more = gridDim.x % 8, xcd = blockIdx.x % 8;
+    const int brick = xcd * share + min(xcd, more) + blockIdx.x / 8;
+    const int prob = brick / per, w = brick % per;
     if (a.act && !a.act[prob]) return;
     const int bx = w % a.b0, by = (w / a.b0) % a.b1, bz = w / (a.b0 * a.b1);
     const double acc = brick_pass<T, NU, POST, RHS, NORM>(a, first, prob, bx, by, bz, lds);
@@ -383,12 +405,14 @@ bool brick_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable)
     if (nu_pre < 1 || nu_pre > 2 || nu_post < 1 || nu_post > 2) return false;
     const int64_t blocks = g->batch * brick_blocks(g, l);
     // Where marches could run, pre + post pass (us, march against bricks): 512 bricks (64^3)
-    // 56 -> 27 FP64 and 49 -> 22 FP32, 1024 (two 64^3 with norms) 63 -> 50 and 54 -> 42, 1728
-    // (96^3) 62 -> 62 and 52 -> 47, 2048 (128 x 128 x 64) 58 -> 68 and 52 -> 52.  On levels
-    // below the marches' sizes, whole cycles against the per-level kernels: 6144 bricks
-    // (96 problems of 32^3) 306 -> 282 and 222 -> 184 us, 8192 (8 x 8 x 65536) 213 -> 221 and
-    // 152 -> 153, 16384 (256 of 32^3) 651 -> 660 and 419 -> 405.
-    return blocks <= (fused3_ok(g, l, variable) ? kBrickMarch : kBrickMost);
+    // 56 -> 25 FP64 and 49 -> 19 FP32, 1024 (two 64^3 with norms) 63 -> 47 and 54 -> 36, 1728
+    // (96^3) 62 -> 54 and 52 -> 41, 2048 (128 x 128 x 64) 58 -> 60 and 52 -> 45, with norms
+    // (four 64^3) 66 -> 82 and 58 -> 55.  On levels below the marches' sizes, whole cycles
+    // against the per-level kernels: 6144 bricks (96 problems of 32^3) 306 -> 255 FP64 and 222
+    // -> 172 FP32, 8192 (8 x 8 x 65536) 213 -> 206 and 152 -> 148, 9216 (48 x 2048 x 48) 312 ->
+    // 288 and 250 -> 202, 32768 (65536 x 16 x 16) 790 -> 1002 and 524 -> 587.
+    if (fused3_ok(g, l, variable)) return blocks <= (g->dtype == FAS_F64 ? kBrickMarch64 : kBrickMarch32);
+    return blocks <= kBrickMost;
 }
 
 int brick_partials(const fas_grid* g, int l) { return (int)brick_blocks(g, l); }
