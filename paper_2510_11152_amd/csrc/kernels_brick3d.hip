@@ -1,27 +1,29 @@
 // Fused 3D passes of small levels (constant kappa) as bricks: a workgroup holds a brick of
-// 8 x 8 x 8 cells with its halo at once (u in LDS, u and f in registers) and runs the pass
+// 8^3 or 16^3 cells with its halo at once (u in LDS, u and f in registers) and runs the pass
 // colour phase by colour phase, one barrier each.  The plane marches (kernels_fused3d.hip)
 // visit a segment's planes one after another, at least (planes + halo) dependent steps, which
 // on a level too small to fill the device is their time: a 64^3 level took two launches of
 // 30 and 26 us a cycle, and a level below the marches' sizes some eleven launches of 5-7 us.
 // A brick pass waits on memory once, then on its phases: V(2,2)-cycles of 64^3 cells
-// 106 -> 49 us (FP64), 95 -> 40 us (FP32), of 32^3 54 -> 29 us, of 48^3 96 -> 37 us.
+// 106 -> 49 us (FP64), 95 -> 40 us (FP32), of 32^3 54 -> 29 us, of 48^3 96 -> 37 us; with
+// bricks of 16^3 (more to do: brick_side) of 96^3 153 -> 68 us, of 128^3 184 -> 111 us.
 //
-// Geometry.  A thread owns a block of 2 x 2 x 2 cells, the children of one coarse cell: half
-// of a cell's neighbours are its registers, the cells that a phase updates are the same for
-// every thread, and the transfers need no neighbour; LDS keeps one plane per cell of the
-// block, indexed by block (as kernels_tail.hip).  A value reaches one cell further along one
-// axis per phase, so a pass reads u within R cells of its brick in the sum of the distances
-// along the axes, not in a cube around it: with two sweeps and the residual (R = 5) 528
-// blocks of the cube's 1000, and f and the phases need fewer still.  The threads are
-// numbered over those blocks only, by a list made at compile time: first the brick's own 64,
-// so that one wave has all of the output work, then the rest in the order of memory (by
-// distance instead: 128^3 FP64 98 -> 80 us for the pre pass; the whole cube: 102 us).  Waves
-// without a boundary face take phases without the selection of their coefficients, and
+// Geometry.  A thread owns a block of 2 x 2 x 2 cells (of large bricks two blocks), the
+// children of one coarse cell: half of a cell's neighbours are its registers, the cells that
+// a phase updates are the same for every thread, and the transfers need no neighbour; LDS
+// keeps one plane per cell of the block, indexed by block (as kernels_tail.hip).  A value
+// reaches one cell further along one axis per phase, so a pass reads u within R cells of its
+// brick in the sum of the distances along the axes, not in a cube around it: with two sweeps
+// and the residual (R = 5) 528 blocks of the cube's 1000 (8^3) or 1984 of 2744 (16^3, whose
+// cube would not fit LDS), and f and the phases need fewer still.  The threads are numbered
+// over those blocks only, by a list made at compile time: first the brick's own, so that few
+// waves have all of the output work, then the rest in the order of memory (by distance
+// instead: 128^3 FP64 in bricks of 8^3 98 -> 80 us for the pre pass; the whole cube: 102 us).
+// Waves without a boundary face take phases without the selection of their coefficients, and
 // neighbours lie at constant LDS offsets (80 -> 76 us); neighbouring bricks run under one L2
-// (76 -> 71 us, the post pass 41 -> 37, 48 problems of 32^3 68 -> 55).  A brick still computes
-// eight times what it writes, 14 us for a pre pass of 64^3 cells and 71 us at 128^3 (march:
-// 45 us): the price of the short chain, hence only small levels.
+// (76 -> 71 us, the post pass 41 -> 37).  Large bricks take 34 and 28 us there (march: 46 and
+// 28), at 256^3 258 us (march: 148): the price of the short chain, hence only small levels.
+// (64 VGPRs, for two large FP32 bricks per compute unit, spill: 22.6 -> 24.9 us.)
 //
 // Passes (Alg. 1): pre = nu sweeps, then u_c = R u and r_c = R (f - A u), on a coarse level
 // forming the FAS right-hand side f = r + A u first; post = u += P (u_c - R u), nu sweeps,
@@ -41,22 +43,23 @@ namespace fas {
 
 namespace {
 
-constexpr int kBrick = 8;            // cells written along each axis
-// Most bricks of a launch on levels that marches take (FP64, FP32), and on smaller ones (brick_ok).
-constexpr int64_t kBrickMarch64 = 1536, kBrickMarch32 = 2048, kBrickMost = 8192;
+// Rules of brick_side and brick_ok, in bricks of 8^3 cells over all problems.
+constexpr int64_t kBrickLarge = 768;                        // from here on bricks of 16^3
+constexpr int64_t kBrickMarch64 = 6144, kBrickMarch64Narrow = 24576, kBrickMarch32 = 4096;  // most where marches could run
+constexpr int64_t kBrickSmallMost = 8192;                   // most of 8^3
 
 // Distance (sum over the axes) from a brick up to which a pass reads u: one cell per colour
 // phase, one more for a residual.  f is read one cell less far.
 constexpr int brick_reach(int nu, bool residual) { return 2 * nu + (residual ? 1 : 0); }
 
-// Blocks of 2 x 2 x 2 cells within reach R of a brick: M along each axis of their bounding
-// cube, N of them in all.
-template <int R>
+// Blocks of 2 x 2 x 2 cells within reach R of a brick of BS^3 cells: M along each axis of
+// their bounding cube, N of them in all, KB to each thread.
+template <int R, int BS>
 struct BrickShape {
-    static constexpr int D = (R + 1) / 2, M = kBrick / 2 + 2 * D;
+    static constexpr int D = (R + 1) / 2, M = BS / 2 + 2 * D;
     static constexpr int out(int i)  // cells between block i of an axis and the brick, plus one (0: inside)
     {
-        const int d = i < D ? D - i : (i >= D + kBrick / 2 ? i - (D + kBrick / 2) + 1 : 0);
+        const int d = i < D ? D - i : (i >= D + BS / 2 ? i - (D + BS / 2) + 1 : 0);
         return d > 0 ? 2 * d - 1 : 0;
     }
     static constexpr int dist(int i, int j, int k) { return out(i) + out(j) + out(k); }
@@ -68,26 +71,59 @@ struct BrickShape {
                 for (int i = 0; i < M; ++i) n += dist(i, j, k) <= R ? 1 : 0;
         return n;
     }
-    static constexpr int N = count(), NT = (N + 63) & ~63;  // threads: one for each block, in whole waves
-    // LDS indices of a plane of cells; with R even the outermost blocks are updated in part, and
-    // what their outer cells would read lies in the padding
-    static constexpr int PAD = R % 2 ? 0 : M * M, CAP = M * M * M + 2 * PAD;
+    static constexpr int N = count();
+    // threads, in whole waves: one for each block; of large bricks for every second one
+    static constexpr int KB = BS > 8 ? 2 : 1, NT = ((N + KB - 1) / KB + 63) & ~63;
+    // LDS indices of one cell of the blocks: rows of M, and of a large brick only the rows that
+    // have blocks (the whole cube would not fit).  Neighbours that no result needs may lie in
+    // other rows, or in the padding.
+    static constexpr bool TRIM = BS > 8;
+    static constexpr int PAD = TRIM ? M + 1 : (R % 2 ? 0 : M * M);
+    static constexpr bool has_row(int j, int k) { return !TRIM || out(j) + out(k) <= R; }
+    static constexpr int index(int i, int j, int k)
+    {
+        int o = PAD + i;
+        for (int z = 0; z < M; ++z)
+            for (int y = 0; y < M; ++y) {
+                if (z > k || (z == k && y >= j)) return o;
+                o += has_row(y, z) ? M : 0;
+            }
+        return o;
+    }
+    static constexpr int CAP = index(0, M, M - 1) + PAD;
 };
 
-// The blocks, the brick's own first, the others in the order of memory (i | j << 4 | k << 8 | distance << 12).
-template <int R>
+// The blocks, the brick's own first, the others in the order of memory: v = i | j << 4 | k << 8
+// | distance << 12; of large bricks w = LDS index | index of the block below << 12 (32-bit
+// entries: above << 12 more).
+template <int R, int BS>
 struct BrickList {
-    unsigned short v[BrickShape<R>::N];
-    constexpr BrickList() : v()
+    using B = BrickShape<R, BS>;
+    unsigned short v[B::N];
+    unsigned short o[B::TRIM ? B::N : 1], below[B::TRIM ? B::N : 1], above[B::TRIM ? B::N : 1];
+    constexpr BrickList() : v(), o(), below(), above()
     {
-        using B = BrickShape<R>;
+        int row[B::M][B::M] = {};  // LDS index of each row
+        for (int k = 0, at = B::PAD; k < B::M; ++k)
+            for (int j = 0; j < B::M; ++j) {
+                row[k][j] = at;
+                at += B::has_row(j, k) ? B::M : 0;
+            }
         int n = 0;
         for (int halo = 0; halo <= 1; ++halo)
             for (int k = 0; k < B::M; ++k)
                 for (int j = 0; j < B::M; ++j)
                     for (int i = 0; i < B::M; ++i) {
                         const int d = B::dist(i, j, k);
-                        if (d <= R && (d > 0) == (halo == 1)) v[n++] = (unsigned short)(i | j << 4 | k << 8 | d << 12);
+                        if (d > R || (d > 0) != (halo == 1)) continue;
+                        v[n] = (unsigned short)(i | j << 4 | k << 8 | d << 12);
+                        if (B::TRIM) {
+                            // (a row that is not there holds nothing a result needs)
+                            o[n] = (unsigned short)(row[k][j] + i);
+                            below[n] = k > 0 && B::has_row(j, k - 1) ? (unsigned short)(row[k - 1][j] + i) : o[n];
+                            above[n] = k < B::M - 1 && B::has_row(j, k + 1) ? (unsigned short)(row[k + 1][j] + i) : o[n];
+                        }
+                        ++n;
                     }
     }
 };
@@ -118,7 +154,8 @@ struct BrickBlock {
     bool on;              // the window has this block
     bool in;              // it lies in the domain (always, on periodic grids)
     bool own;             // the brick writes it
-    int o;                // LDS index of the block
+    int dist;             // of its nearest cell from the brick
+    int o, zm, zp;        // LDS index of the block, and (large bricks) of those below and above
     bool lo[3], hi[3];    // the cells at 0 / at 1 along an axis have a boundary face
     unsigned row[4];      // byte offsets of its cell pairs in the domain (wrapped or clamped)
     unsigned coarse;      // and of its coarse cell
@@ -126,12 +163,14 @@ struct BrickBlock {
 };
 
 // The pass of one brick; returns the thread's share of the sum of r^2.
-template <typename T, int NU, bool POST, bool RHS, bool NORM>
+template <typename T, int NU, bool POST, bool RHS, bool NORM, int BS>
 __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, int prob, int bx, int by, int bz, T* lds)
 {
     constexpr bool RES = !POST || NORM;
-    constexpr int R = brick_reach(NU, RES), D = BrickShape<R>::D, M = BrickShape<R>::M, CAP = BrickShape<R>::CAP;
-    static constexpr BrickList<R> list{};
+    constexpr int R = brick_reach(NU, RES);
+    using Shape = BrickShape<R, BS>;
+    constexpr int D = Shape::D, M = Shape::M, CAP = Shape::CAP, KB = Shape::KB;
+    static constexpr BrickList<R, BS> list{};
     static_assert(!(POST && RHS), "a pre pass forms the right-hand side");
     // a row's cell pair (base pointers need not be aligned to pairs)
     typedef T V __attribute__((ext_vector_type(2), aligned(sizeof(T))));
@@ -154,14 +193,15 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
         return all ? v3 : (two ? v2 : (any ? v1 : v0));
     };
     auto nb_sum = [&](const BrickBlock<T>& B, int c) {
+        const int below[3] = {B.o - 1, B.o - M, Shape::TRIM ? B.zm : B.o - M * M};
+        const int above[3] = {B.o + 1, B.o + M, Shape::TRIM ? B.zp : B.o + M * M};
         T v[6];
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
             const int o = c ^ (1 << x);
             const bool hi = (c >> x) & 1;
-            constexpr int step[3] = {1, M, M * M};
-            v[2 * x] = hi ? B.u[o] : U(o)[B.o - step[x]];
-            v[2 * x + 1] = hi ? U(o)[B.o + step[x]] : B.u[o];
+            v[2 * x] = hi ? B.u[o] : U(o)[below[x]];
+            v[2 * x + 1] = hi ? U(o)[above[x]] : B.u[o];
         }
         return nbsum<T, 3>(v);
     };
@@ -172,20 +212,25 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
     };
 
     // every load is issued before the first use
-    BrickBlock<T> b;
-    T cnew = (T)0;
-    int dist;  // of the block's nearest cell
-    {
-        const int t = (int)threadIdx.x;
-        b.on = t < BrickShape<R>::N;
-        const int code = list.v[b.on ? t : 0];
-        dist = code >> 12;
+    BrickBlock<T> blk[KB];
+    T cnew[KB];
+    bool faces = false;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+        BrickBlock<T>& b = blk[kb];
+        const int t = (int)threadIdx.x + kb * Shape::NT;
+        b.on = t < Shape::N;
+        const int at = b.on ? t : 0, code = list.v[at];
+        b.dist = code >> 12;
         const int pos[3] = {code & 15, code >> 4 & 15, code >> 8 & 15};
-        const int org[3] = {bx * kBrick - 2 * D, by * kBrick - 2 * D, bz * kBrick - 2 * D};
+        const int org[3] = {bx * BS - 2 * D, by * BS - 2 * D, bz * BS - 2 * D};
         int g[3];
-        b.o = BrickShape<R>::PAD + pos[0] + M * (pos[1] + M * pos[2]);
+        if constexpr (Shape::TRIM)
+            b.o = list.o[at], b.zm = list.below[at], b.zp = list.above[at];
+        else
+            b.o = Shape::PAD + pos[0] + M * (pos[1] + M * pos[2]);
         b.in = b.on;
-        b.own = b.on && dist == 0;
+        b.own = b.on && b.dist == 0;
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
             g[x] = org[x] + 2 * pos[x];
@@ -198,6 +243,7 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
                 b.in = b.in && g[x] >= 0 && g[x] < n[x];
                 g[x] = min(max(g[x], 0), n[x] - 2);
             }
+            faces = faces || b.lo[x] || b.hi[x];
         }
         const unsigned first_cell = g[0] + (unsigned)a.n0 * (g[1] + (unsigned)a.n1 * g[2]);
         b.coarse = (g[0] / 2 + (unsigned)(a.n0 / 2) * (g[1] / 2 + (unsigned)(a.n1 / 2) * (g[2] / 2))) * sizeof(T);
@@ -205,52 +251,60 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
         for (int i = 0; i < 4; ++i) {
             b.row[i] = (first_cell + (i & 1) * (unsigned)a.n0 + (i >> 1) * (unsigned)(a.n0 * a.n1)) * sizeof(T);
             V vu = {(T)0, (T)0}, vf = {(T)0, (T)0};
-            if (b.in && dist < R) vf = *pair_at(a.f, b.row[i]);
+            if (b.in && b.dist < R) vf = *pair_at(a.f, b.row[i]);
             if (b.in && !(sizeof(T) == 4 && a.zero_in)) vu = *pair_at(a.u_in, b.row[i]);
             b.u[2 * i] = vu.x;
             b.u[2 * i + 1] = vu.y;
             b.f[2 * i] = vf.x;
             b.f[2 * i + 1] = vf.y;
         }
-        if constexpr (POST) cnew = *coarse_at(a.uc, b.coarse);
+        if constexpr (POST) cnew[kb] = *coarse_at(a.uc, b.coarse);
     }
     // whether any block of the wave has a boundary face
-    const bool walls = __any(b.lo[0] || b.hi[0] || b.lo[1] || b.hi[1] || b.lo[2] || b.hi[2]) != 0;
+    const bool walls = __any(faces) != 0;
     auto with_walls = [&](auto&& body) {
         if (walls)
             body(std::true_type{});
         else
             body(std::false_type{});
     };
-    if constexpr (POST) {
-        // the fine grid correction: the block's cells are the children of one coarse cell
-        const T c = cnew - restrict8(b.u[0], b.u[1], b.u[2], b.u[3], b.u[4], b.u[5], b.u[6], b.u[7]);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) b.u[i] = b.in ? b.u[i] + c : b.u[i];
-    }
-    if (b.on) {
+    for (int kb = 0; kb < KB; ++kb) {
+        BrickBlock<T>& b = blk[kb];
+        if constexpr (POST) {
+            // the fine grid correction: the block's cells are the children of one coarse cell
+            const T c = cnew[kb] - restrict8(b.u[0], b.u[1], b.u[2], b.u[3], b.u[4], b.u[5], b.u[6], b.u[7]);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) U(c)[b.o] = b.u[c];
+            for (int i = 0; i < 8; ++i) b.u[i] = b.in ? b.u[i] + c : b.u[i];
+        }
+        if (b.on) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) U(c)[b.o] = b.u[c];
+        }
     }
     __syncthreads();
     if constexpr (RHS) {
         // FAS right-hand side from the initial values: f = r + A u
-        with_walls([&](auto wl) {
-            if (dist >= R) return;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) b.f[c] = b.f[c] + apply(wl, b, c);
-        });
-        if (b.own) {
+        for (int kb = 0; kb < KB; ++kb) {
+            BrickBlock<T>& b = blk[kb];
+            with_walls([&](auto wl) {
+                if (b.dist >= R) return;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) *pair_at(a.fout, b.row[i]) = V{b.f[2 * i], b.f[2 * i + 1]};
+                for (int c = 0; c < 8; ++c) b.f[c] = b.f[c] + apply(wl, b, c);
+            });
+            if (b.own) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *pair_at(a.fout, b.row[i]) = V{b.f[2 * i], b.f[2 * i + 1]};
+            }
         }
         __syncthreads();
     }
     // colour phases
-    auto phase = [&](auto step, auto par, auto wl) {
+    auto phase = [&](auto step, auto par, auto wl, BrickBlock<T>& b) {
         constexpr int s = decltype(step)::value, P = decltype(par)::value;
         // blocks outside the domain stay 0; from this far off no value reaches a result any more
-        if (!b.in || dist > R - 1 - s) return;
+        if (!b.in || b.dist > R - 1 - s) return;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             if ((((c & 1) + ((c >> 1) & 1) + (c >> 2)) & 1) != P) continue;
@@ -260,10 +314,13 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
     };
     auto colour = [&](auto step) {
         with_walls([&](auto wl) {
-            if (((decltype(step)::value & 1) ^ first) != 0)
-                phase(step, std::integral_constant<int, 1>{}, wl);
-            else
-                phase(step, std::integral_constant<int, 0>{}, wl);
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                if (((decltype(step)::value & 1) ^ first) != 0)
+                    phase(step, std::integral_constant<int, 1>{}, wl, blk[kb]);
+                else
+                    phase(step, std::integral_constant<int, 0>{}, wl, blk[kb]);
+            }
         });
         __syncthreads();
     };
@@ -273,6 +330,9 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
         colour(std::integral_constant<int, 2>{});
         colour(std::integral_constant<int, 3>{});
     }
+    // (a thread's own block is its first)
+    static_assert(BS * BS * BS / 8 <= Shape::NT, "own blocks");
+    const BrickBlock<T>& b = blk[0];
     double acc = 0.0;
     if (b.own) {
 #pragma unroll
@@ -303,10 +363,14 @@ __device__ __forceinline__ double brick_pass(const BrickArgs<T>& a, int first, i
     return acc;
 }
 
-template <typename T, int NU, bool POST, bool RHS, bool NORM>
-__global__ __launch_bounds__(BrickShape<brick_reach(NU, !POST || NORM)>::NT) void k_brick(BrickArgs<T> a, int first)
+// threads of a pass's workgroup
+template <int NU, bool RES, int BS>
+constexpr int kBrickThreads = BrickShape<brick_reach(NU, RES), BS>::NT;
+
+template <typename T, int NU, bool POST, bool RHS, bool NORM, int BS>
+__global__ __launch_bounds__((kBrickThreads<NU, !POST || NORM, BS>)) void k_brick(BrickArgs<T> a, int first)
 {
-    using B = BrickShape<brick_reach(NU, !POST || NORM)>;
+    using B = BrickShape<brick_reach(NU, !POST || NORM), BS>;
     __shared__ T lds[8 * B::CAP];
     const int per = a.b0 * a.b1 * a.b2;
     // neighbouring bricks share most of what they read: each of the 8 L2 caches (blocks go to
@@ -316,12 +380,25 @@ __global__ __launch_bounds__(BrickShape<brick_reach(NU, !POST || NORM)>::NT) voi
     const int prob = brick / per, w = brick % per;
     if (a.act && !a.act[prob]) return;
     const int bx = w % a.b0, by = (w / a.b0) % a.b1, bz = w / (a.b0 * a.b1);
-    const double acc = brick_pass<T, NU, POST, RHS, NORM>(a, first, prob, bx, by, bz, lds);
+    const double acc = brick_pass<T, NU, POST, RHS, NORM, BS>(a, first, prob, bx, by, bz, lds);
     if constexpr (NORM) {
-        // the brick's own blocks are the first wave's: a fixed butterfly over its lanes
+        // the brick's own blocks are the first waves': a fixed butterfly over the lanes of each,
+        // then the waves in order
+        constexpr int OWN = BS * BS * BS / 8 / 64;
+        __shared__ double red[OWN];
         double v = acc;
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (threadIdx.x == 0) a.partials[(int64_t)prob * per + w] = v;
+        if constexpr (OWN == 1) {
+            if (threadIdx.x == 0) a.partials[(int64_t)prob * per + w] = v;
+        } else {
+            if ((int)threadIdx.x < 64 * OWN && (threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                double s = 0.0;
+                for (int i = 0; i < OWN; ++i) s += red[i];
+                a.partials[(int64_t)prob * per + w] = s;
+            }
+        }
     }
 }
 
@@ -331,9 +408,30 @@ inline void check_launch()
     if (e != hipSuccess) throw Error(FAS_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
 }
 
+// Bricks of level l of bs^3 cells, for one problem.
+int64_t brick_blocks(const fas_grid* g, int l, int bs)
+{
+    int64_t n = 1;
+    for (int a = 0; a < 3; ++a) n *= (g->lev[l].n[a] + bs - 1) / bs;
+    return n;
+}
+
+// Cells along the axes of level l's bricks: large ones compute 3.9 times what they write, small
+// ones 8.25 times, but a large one takes 13 us on a compute unit to itself, two small ones 8.
+// Pre + post pass, small against large: 512 small bricks (64^3) 25 and 29 us (FP64), 19 and 24
+// (FP32), 768 (96 x 64 x 64) 31 and 31, 25 and 24, 1024 (two 64^3 with norms) 47 and 35, 36
+// and 28.  Bricks that a level's axes leave mostly empty are not worth it (one axis of 8: 108
+// and 91 us; two: 189 and 261).
+int brick_side(const fas_grid* g, int l)
+{
+    const int64_t small = brick_blocks(g, l, 8);
+    return g->batch * small >= kBrickLarge && small >= 3 * brick_blocks(g, l, 16) ? 16 : 8;
+}
+
 template <typename T>
 BrickArgs<T> make_brick_args(const fas_grid* g, int l, const Coef& c)
 {
+    const int bs = brick_side(g, l);
     BrickArgs<T> a{};
     a.n0 = g->lev[l].n[0];
     a.n1 = g->lev[l].n[1];
@@ -341,27 +439,36 @@ BrickArgs<T> make_brick_args(const fas_grid* g, int l, const Coef& c)
     a.bc = g->bc;
     a.k = (T)c.kd;
     for (int no = 0; no < 4; ++no) a.q[no] = (T)c.q[diag_count(g->bc, 3, no)];
-    a.b0 = (a.n0 + kBrick - 1) / kBrick;
-    a.b1 = (a.n1 + kBrick - 1) / kBrick;
-    a.b2 = (a.n2 + kBrick - 1) / kBrick;
+    a.b0 = (a.n0 + bs - 1) / bs;
+    a.b1 = (a.n1 + bs - 1) / bs;
+    a.b2 = (a.n2 + bs - 1) / bs;
     a.stride = g->lev[l].N;
     a.cstride = g->lev[l + 1].N;
     a.act = active_flags(g);
     return a;
 }
 
-template <typename T, bool POST, bool RHS, bool NORM>
-void launch_brick(const fas_grid* g, const BrickArgs<T>& a, int nu, int first)
+template <typename T, bool POST, bool RHS, bool NORM, int BS>
+void launch_brick_side(const fas_grid* g, const BrickArgs<T>& a, int nu, int first)
 {
     const unsigned blocks = (unsigned)((int64_t)g->batch * a.b0 * a.b1 * a.b2);
     constexpr bool RES = !POST || NORM;
     if (nu == 1)
-        k_brick<T, 1, POST, RHS, NORM><<<blocks, BrickShape<brick_reach(1, RES)>::NT, 0, g->stream>>>(a, first);
+        k_brick<T, 1, POST, RHS, NORM, BS><<<blocks, kBrickThreads<1, RES, BS>, 0, g->stream>>>(a, first);
     else if (nu == 2)
-        k_brick<T, 2, POST, RHS, NORM><<<blocks, BrickShape<brick_reach(2, RES)>::NT, 0, g->stream>>>(a, first);
+        k_brick<T, 2, POST, RHS, NORM, BS><<<blocks, kBrickThreads<2, RES, BS>, 0, g->stream>>>(a, first);
     else
         throw Error(FAS_ERR_ARG, "internal: brick passes take one or two sweeps");
     check_launch();
+}
+
+template <typename T, bool POST, bool RHS, bool NORM>
+void launch_brick(const fas_grid* g, int l, const BrickArgs<T>& a, int nu, int first)
+{
+    if (brick_side(g, l) == 8)
+        launch_brick_side<T, POST, RHS, NORM, 8>(g, a, nu, first);
+    else
+        launch_brick_side<T, POST, RHS, NORM, 16>(g, a, nu, first);
 }
 
 template <typename T>
@@ -372,9 +479,9 @@ void brick_pre(const fas_grid* g, int l, const Coef& c, int first, int nu, const
     a.f = (const T*)f, a.u_in = (const T*)u_in, a.u_out = (T*)u_out;
     a.uc = (T*)uc, a.rc = (T*)rc, a.fout = (T*)fout, a.zero_in = zero ? 1 : 0;
     if (fout)
-        launch_brick<T, false, true, false>(g, a, nu, first);
+        launch_brick<T, false, true, false>(g, l, a, nu, first);
     else
-        launch_brick<T, false, false, false>(g, a, nu, first);
+        launch_brick<T, false, false, false>(g, l, a, nu, first);
 }
 
 template <typename T>
@@ -385,16 +492,9 @@ void brick_post(const fas_grid* g, int l, const Coef& c, int first, int nu, cons
     a.f = (const T*)f, a.u_in = (const T*)u_in, a.u_out = (T*)u_out;
     a.uc = (T*)const_cast<void*>(uc), a.partials = partials, a.acc64 = acc64;
     if (partials)
-        launch_brick<T, true, false, true>(g, a, nu, first);
+        launch_brick<T, true, false, true>(g, l, a, nu, first);
     else
-        launch_brick<T, true, false, false>(g, a, nu, first);
-}
-
-int64_t brick_blocks(const fas_grid* g, int l)
-{
-    int64_t n = 1;
-    for (int a = 0; a < 3; ++a) n *= (g->lev[l].n[a] + kBrick - 1) / kBrick;
-    return n;
+        launch_brick<T, true, false, false>(g, l, a, nu, first);
 }
 
 }  // namespace
@@ -403,19 +503,25 @@ bool brick_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable)
 {
     if (!g->fused || g->dim != 3 || variable || l >= g->L) return false;
     if (nu_pre < 1 || nu_pre > 2 || nu_post < 1 || nu_post > 2) return false;
-    const int64_t blocks = g->batch * brick_blocks(g, l);
-    // Where marches could run, pre + post pass (us, march against bricks): 512 bricks (64^3)
-    // 56 -> 25 FP64 and 49 -> 19 FP32, 1024 (two 64^3 with norms) 63 -> 47 and 54 -> 36, 1728
-    // (96^3) 62 -> 54 and 52 -> 41, 2048 (128 x 128 x 64) 58 -> 60 and 52 -> 45, with norms
-    // (four 64^3) 66 -> 82 and 58 -> 55.  On levels below the marches' sizes, whole cycles
-    // against the per-level kernels: 6144 bricks (96 problems of 32^3) 306 -> 255 FP64 and 222
-    // -> 172 FP32, 8192 (8 x 8 x 65536) 213 -> 206 and 152 -> 148, 9216 (48 x 2048 x 48) 312 ->
-    // 288 and 250 -> 202, 32768 (65536 x 16 x 16) 790 -> 1002 and 524 -> 587.
-    if (fused3_ok(g, l, variable)) return blocks <= (g->dtype == FAS_F64 ? kBrickMarch64 : kBrickMarch32);
-    return blocks <= kBrickMost;
+    if (g->lev[l].N * (int64_t)g->elem() > 0xffffffffll) return false;  // 32-bit byte offsets
+    const int64_t blocks = g->batch * brick_blocks(g, l, 8);
+    // Where marches could run, pre + post pass (us, march against bricks): FP64 512 bricks
+    // (64^3) 56 -> 25, 1728 (96^3) 62 -> 33, 4096 (128^3) 74 -> 63, 6144 (192 x 128 x 128) 87
+    // and 87, 8000 (160^3) 104 and 113, 32768 (256^3) 262 and 469; marches leave two tiles half
+    // empty on 64 columns: 8192 (16 problems of 64^3, norms) 152 -> 123, 24576 (48) 415 -> 358,
+    // 49152 683 and 704.  FP32 512 49 -> 19, 4096 54 -> 43, 6144 59 and 60, 8192 (16 of 64^3)
+    // 78 and 82.
+    if (fused3_ok(g, l, variable))
+        return blocks <= (g->dtype == FAS_F32 ? kBrickMarch32
+                                              : (g->lev[l].n[0] <= 64 ? kBrickMarch64Narrow : kBrickMarch64));
+    // Elsewhere whole cycles against the per-level kernels: 1024 problems of 32^3 2388 -> 848 us
+    // (FP64) and 1367 -> 681 (FP32), 48 x 48 x 8192 1430 -> 587, 65536 x 16 x 16 788 -> 496; with
+    // small bricks 8 x 8 x 65536 (8192 of them) 213 -> 206 and 152 -> 148, twice as many the same
+    // or slower.
+    return brick_side(g, l) == 16 || blocks <= kBrickSmallMost;
 }
 
-int brick_partials(const fas_grid* g, int l) { return (int)brick_blocks(g, l); }
+int brick_partials(const fas_grid* g, int l) { return (int)brick_blocks(g, l, brick_side(g, l)); }
 
 void launch_brick_pre(const fas_grid* g, int l, const Coef& c, int first, int nu, const void* f, const void* u_in,
                       void* u_out, void* uc, void* rc, void* fout, bool zero)
