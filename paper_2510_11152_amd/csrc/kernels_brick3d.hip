@@ -45,7 +45,7 @@ namespace {
 
 // Rules of brick_side and brick_ok, in bricks of 8^3 cells over all problems.
 constexpr int64_t kBrickLarge = 768;                        // from here on bricks of 16^3
-constexpr int64_t kBrickMarch64 = 6144, kBrickMarch64Narrow = 24576, kBrickMarch32 = 4096;  // most where marches could run
+constexpr int64_t kBrickMarch = 6144, kBrickMarchNarrow = 24576, kBrickMarch32 = 4096;  // most where marches could run
 constexpr int64_t kBrickSmallMost = 8192;                   // most of 8^3
 
 // Distance (sum over the axes) from a brick up to which a pass reads u: one cell per colour
@@ -510,10 +510,13 @@ bool brick_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable)
     // and 87, 8000 (160^3) 104 and 113, 32768 (256^3) 262 and 469; marches leave two tiles half
     // empty on 64 columns: 8192 (16 problems of 64^3, norms) 152 -> 123, 24576 (48) 415 -> 358,
     // 49152 683 and 704.  FP32 512 49 -> 19, 4096 54 -> 43, 6144 59 and 60, 8192 (16 of 64^3)
-    // 78 and 82.
-    if (fused3_ok(g, l, variable))
-        return blocks <= (g->dtype == FAS_F32 ? kBrickMarch32
-                                              : (g->lev[l].n[0] <= 64 ? kBrickMarch64Narrow : kBrickMarch64));
+    // 78 and 82; but below the finest level marches need a pass more for the right-hand side:
+    // cycles of 384 x 256 x 256 with 6144 bricks there 393 -> 379, of 48 problems of 128^3 with
+    // 24576 of 64 columns 1600 -> 1516, of 384^3 with 13824 732 and 746.
+    if (fused3_ok(g, l, variable)) {
+        if (g->dtype == FAS_F32 && l == 0) return blocks <= kBrickMarch32;
+        return blocks <= (g->lev[l].n[0] <= 64 ? kBrickMarchNarrow : kBrickMarch);
+    }
     // Elsewhere whole cycles against the per-level kernels: 1024 problems of 32^3 2388 -> 848 us
     // (FP64) and 1367 -> 681 (FP32), 48 x 48 x 8192 1430 -> 587, 65536 x 16 x 16 788 -> 496; with
     // small bricks 8 x 8 x 65536 (8192 of them) 213 -> 206 and 152 -> 148, twice as many the same
