@@ -127,9 +127,9 @@ int plan(int dim, const int64_t n[3], int dtype, int coarsest, int flags, int ba
         lay->mix_r = off;
         off = align_up(off + N0 * s);
     }
-    // one partial sum per fused tile (3D tiles write at least 52 x 20 cells of a plane,
-    // segments of 64 planes, 32 when the grid is small), per 2D march wave (kStripCols x
-    // kMinSegRows cells at least) or per block of the stand-alone norm kernel
+    // one partial sum per fused tile (3D marches write at least 52 x 20 cells of a plane), per
+    // 2D march wave (kStripCols x kMinSegRows cells at least) or per block of the stand-alone
+    // norm kernel; a 3D pass with more blocks than that leaves the norm to that kernel
     int64_t tiles = 1;
     if (dim == 3)
         tiles = ((n[0] + 51) / 52) * ((n[1] + 19) / 20) * ((n[2] + 31) / 32);
