@@ -550,7 +550,7 @@ def bench_ns(dev, n=4096, re=10.0, dts=(0.1, 0.05, 0.025, 0.0125, 0.00625), cpu=
     pre_us, post_us, timed = S.profile()
     fine = S.shape[0] * S.shape[1]
     coarse = (n // 2) * (n // 2 - 1)
-    alg_pre = 24.0 * fine + 24.0 * coarse    # read w, f; write w; write R w (twice) and R r
+    alg_pre = 24.0 * fine + 16.0 * coarse    # read w, f; write w; write R w and R r
     alg_post = 24.0 * fine + 16.0 * coarse   # read w, f and the coarse iterate and its copy; write w
     out["finest_kernels"] = {
         "grid": list(S.shape), "cycles_timed": timed,
