@@ -24,6 +24,8 @@
 #include <hip/hip_runtime.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "fas_batch.h"
 #include "fas_device.h"
 #include "fas_internal.h"
@@ -69,13 +71,23 @@ struct TailArgs {
     const int* act;           // per-problem active flags (nullable)
 };
 
-// Blocks one LDS plane holds, and blocks a thread owns on the largest level.  Small: tails
-// from at most 64^2 or 16^3 cells; big: the largest levels tail_top() admits.
+// Blocks one LDS plane holds, and blocks a thread owns on the largest level of a tail of
+// several levels (tail_kb) and of a coarsest level alone (tail_kb_one).  Small: tails from at
+// most 64^2 or 16^3 cells; big: all that the byte budget admits (tail_class).  A coarsest level
+// alone may take the whole budget, and an odd axis of it ends in half blocks: up to 1554 blocks
+// in FP64 and 3087 in FP32 (2D, constant kappa), where the top of several levels has at most
+// 1228 and 2457.  Cycles with such a tail against the cell-per-thread form: 220^2 FP32
+// (coarsest 110) 50 -> 46 us, 148 x 166 FP64 (coarsest 74) 46 -> 39 us, 36 x 1200 FP32
+// (coarsest 18) 81 -> 44 us.
 constexpr int tail_cap(int dim, bool big, size_t s)
 {
-    return dim == 2 ? (!big ? 1368 : (s == 8 ? 1568 : 3120)) : (!big ? 600 : (s == 8 ? 1104 : 2224));
+    return dim == 2 ? (!big ? 1368 : (s == 8 ? 1568 : 3120)) : (!big ? 600 : (s == 8 ? 1112 : 2224));
 }
 constexpr int tail_kb(int dim, bool big, size_t s) { return !big ? (dim == 2 ? 2 : 1) : (s == 8 ? 3 : 5); }
+constexpr int tail_kb_one(int dim, bool big, size_t s, bool kv)
+{
+    return big && dim == 2 && !kv ? (s == 8 ? 4 : 7) : tail_kb(dim, big, s);
+}
 
 __device__ __forceinline__ int div_by(int t, unsigned g) { return g ? (int)__umulhi((unsigned)t, g) : t; }
 
@@ -101,6 +113,7 @@ template <typename T, int DIM, bool KV, bool BIG>
 struct Tail {
     static constexpr int C = 1 << DIM;
     static constexpr int CAP = tail_cap(DIM, BIG, sizeof(T)), KB = tail_kb(DIM, BIG, sizeof(T));
+    static constexpr int KB1 = tail_kb_one(DIM, BIG, sizeof(T), KV);
     static constexpr int PLANES = (KV ? 3 : 2) * C;
     using Block = TailBlock<T, DIM, KV, BIG>;
     using Level = TailLevel<T>;
@@ -497,7 +510,7 @@ struct Tail {
             }
             __syncthreads();
         } else {
-            coarsest<KB, false>(last ? nullptr : u_top, last ? nullptr : r_top, last ? nullptr : u_top);
+            coarsest<KB1, false>(last ? nullptr : u_top, last ? nullptr : r_top, last ? nullptr : u_top);
         }
         for (int l = (a.one < last ? a.one : last) - 1; l >= 0; --l) up<KB, false>(l, l ? nullptr : u_top);
     }
@@ -688,15 +701,6 @@ __global__ __launch_bounds__(kTailThreadsK3) void k_tail_k3(TailArgsK3<T> a)
 
 unsigned div_magic(int64_t d) { return d > 1 ? (unsigned)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d) : 0u; }
 
-// Whether the tail of args a takes the big planes (set by make_tail_args).
-template <typename T>
-bool tail_is_big(const TailArgs<T>& a, int dim)
-{
-    const TailLevel<T>& last = a.lev[a.nl - 1];
-    return a.lev[0].nb > kTailThreads * tail_kb(dim, false, sizeof(T)) ||
-           last.off + last.nb > tail_cap(dim, false, sizeof(T));
-}
-
 template <typename T>
 TailArgs<T> make_tail_args(const fas_grid* g, int top, const Coef* coef, int pre, int post, int first)
 {
@@ -728,9 +732,7 @@ TailArgs<T> make_tail_args(const fas_grid* g, int top, const Coef* coef, int pre
         L.kap = (const T*)g->lev[l].kap;
         if (L.nb <= 64 && a.one == a.nl) a.one = i;
     }
-    const bool big = tail_is_big(a, g->dim);
-    if (off > tail_cap(g->dim, big, sizeof(T)) || a.lev[0].nb > kTailThreads * tail_kb(g->dim, big, sizeof(T)))
-        throw Error(FAS_ERR_ARG, "internal: tail levels exceed the tail's LDS");
+    if (tail_class(g, top) < 0) throw Error(FAS_ERR_ARG, "internal: tail levels exceed the tail's LDS");
     return a;
 }
 
@@ -794,7 +796,7 @@ void launch_t(const fas_grid* g, int top, const Coef* coef, int pre, int post, i
     a.form_rhs = form_rhs;
     a.stride = g->lev[top].N;
     a.act = active_flags(g);
-    const bool big = tail_is_big(a, g->dim);
+    const bool big = tail_class(g, top) == 1;
 #define FAS_TAIL(DIM_, KV_)                                                             \
     do {                                                                                \
         if (big)                                                                        \
@@ -814,11 +816,29 @@ void launch_t(const fas_grid* g, int top, const Coef* coef, int pre, int post, i
 
 }  // namespace
 
+int tail_class(const fas_grid* g, int top)
+{
+    const bool kv = (g->flags & FAS_FLAG_VARIABLE_KAPPA) != 0;
+    const size_t s = g->elem();
+    int64_t blocks = 1, most = 0;  // block 0: the zeros across a boundary
+    for (int l = top; l <= g->L; ++l) {
+        int64_t nb = 1;
+        for (int a = 0; a < g->dim; ++a) nb *= (g->lev[l].n[a] + 1) / 2;
+        blocks += nb;
+        most = std::max(most, nb);
+    }
+    for (int big = 0; big < 2; ++big) {
+        const int kb = top == g->L ? tail_kb_one(g->dim, big, s, kv) : tail_kb(g->dim, big, s);
+        if (blocks <= tail_cap(g->dim, big, s) && most <= (int64_t)kTailThreads * kb) return big;
+    }
+    return -1;
+}
+
 int tail_top(const fas_grid* g)
 {
     // the largest level from which every coarser level's u and f (and, on a grid that may
     // take a cell kappa, the top level's face tables in 2D or every level's kappa in 3D) fit
-    // the tail's LDS; the budgets admit the same levels
+    // the budget in bytes, and whose blocks the planes and the threads hold
     const size_t s = g->elem();
     const bool kv = (g->flags & FAS_FLAG_VARIABLE_KAPPA) != 0;
     const size_t cap = kv ? (size_t)kTailLdsKV : (size_t)kTailLds;
@@ -828,7 +848,7 @@ int tail_top(const fas_grid* g)
         bytes += (kv && g->dim == 3 ? 3 : 2) * (size_t)g->lev[l].N * s;
         const int64_t n0 = g->lev[l].n[0], n1 = g->lev[l].n[1];
         const size_t faces = kv && g->dim == 2 ? (size_t)((n0 + 1) * n1 + n0 * (n1 + 1)) * s : 0;
-        if (bytes + faces > cap || g->L - l + 1 > kMaxTail) break;
+        if (bytes + faces > cap || g->L - l + 1 > kMaxTail || tail_class(g, l) < 0) break;
         top = l;
     }
     return top;  // L + 1: not even the coarsest level fits
@@ -850,7 +870,7 @@ bool fill_tail_desc_t(const fas_grid* g, int top, const Coef* coef, int pre, int
     a.stride = 0;
     a.act = act;
     memcpy(out, &a, sizeof(a));
-    return tail_is_big(a, g->dim);
+    return tail_class(g, top) == 1;
 }
 
 bool fill_tail_desc(const fas_grid* g, int top, const Coef* coef, int pre, int post, int first, void* u, const void* r,

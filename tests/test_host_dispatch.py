@@ -1,0 +1,87 @@
+"""Host-side rules that choose a grid's kernels, checked without a GPU (grids are planned over
+a workspace that nothing touches)."""
+import ctypes
+import itertools
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_2510_11152_amd import _lib
+    if not os.path.exists(_lib.LIB_PATH):
+        pytest.fail("libfas.so is not built (run __graft_entry__.build())")
+    return _lib.load()
+
+
+class Planned:
+    def __init__(self, lib, n, f32, coarsest, flags=0):
+        self.lib, self.handle = lib, ctypes.c_void_p()
+        n3 = (ctypes.c_int64 * 3)(*(list(n) + [1] * (3 - len(n))))
+        need = lib.fas_workspace_size(len(n), n3, int(f32), coarsest, flags)
+        assert need, (n, coarsest)
+        fake = ctypes.c_void_p(1 << 20)  # never dereferenced
+        assert lib.fas_grid_create(len(n), n3, 1.0, 0, int(f32), coarsest, flags, fake, need, None,
+                                   ctypes.byref(self.handle)) == 0
+
+    def __enter__(self):
+        return self.handle
+
+    def __exit__(self, *exc):
+        self.lib.fas_grid_destroy(self.handle)
+
+
+def tail_top_by_bytes(n, L, f32, variable):
+    """First level of the tail by its budget alone: u and f of all its levels and, on a grid for
+    a cell kappa, the top level's face weights (2D) or every level's kappa (3D)."""
+    s, dim = 4 if f32 else 8, len(n)
+    used, top = 0, L + 1
+    for l in range(L, -1, -1):
+        m = [x >> l for x in n]
+        cells = m[0] * m[1] * (m[2] if dim == 3 else 1)
+        used += (3 if variable and dim == 3 else 2) * cells * s
+        faces = ((m[0] + 1) * m[1] + m[0] * (m[1] + 1)) * s if variable and dim == 2 else 0
+        if used + faces > (156 if variable else 96) * 1024 or L - l + 1 > 10:
+            break
+        top = l
+    return top
+
+
+def hierarchies(f32, variable):
+    """Coarsest levels of every shape up to and past the budget, one to three levels above."""
+    most = (156 if variable else 96) * 1024 // (2 * (4 if f32 else 8))
+    for c in range(2, int(most ** 0.5) + 1, 4):
+        longest = most // c
+        for m in sorted({c, c + 1, longest // 5, longest // 4, longest // 3, longest // 2} |
+                        set(range(max(c, longest - 12), longest + 3))):
+            if m < c:
+                continue
+            for L in (1, 2, 4):
+                yield (c << L, m << L), c, L
+                yield (m << L, c << L), c, L
+    for c, m in itertools.product((2, 4, 6, 10, 18), (0, 1, 2, 5)):
+        longest = most // (c * (c + m))
+        for k in sorted({c + m, longest // 9, longest // 8, longest // 4, longest // 2} |
+                        set(range(max(c + m, longest - 12), longest + 3))):
+            if k < c + m:
+                continue
+            for L in (1, 2):
+                yield (c << L, (c + m) << L, k << L), c, L
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("variable", [False, True])
+def test_tail_holds_every_level_its_budget_admits(lib, f32, variable):
+    """No level that the byte budget admits is left without planes or threads for its blocks."""
+    tail_top = lib["_ZN3fas8tail_topEPK8fas_grid"]
+    tail_class = lib["_ZN3fas10tail_classEPK8fas_gridi"]
+    tail_top.argtypes, tail_class.argtypes = [ctypes.c_void_p], [ctypes.c_void_p, ctypes.c_int]
+    seen = set()
+    for n, c, L in hierarchies(f32, variable):
+        with Planned(lib, n, f32, c, flags=int(variable)) as g:
+            want = tail_top_by_bytes(n, L, f32, variable)
+            assert tail_top(g) == want, (n, c)
+            if want <= L:
+                seen.add(tail_class(g, want))
+    assert seen == {0, 1}
