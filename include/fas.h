@@ -83,14 +83,17 @@ extern "C" {
                                    and keep the fastest (cached per process): for block
                                    tiles the waves per block (6, 8, 12, 16; cell kappa 6,
                                    8) and the strips per group of the tile order (4, 8,
-                                   16, 32), for row marches the segment height;
-                                   0 (default): fixed rules                               */
+                                   16, 32), for row and plane marches the segment height
+                                   (the brick passes of small 3D levels have nothing to
+                                   time); 0 (default): fixed rules                        */
 #define FAS_OPT_SEG_ROWS 7       /* > 0 (even, >= 8): rows (2D) / planes (3D) per segment of
-                                   every march launch, overriding rule and autotuner;
-                                   0 (default): rule or autotuner                         */
+                                   every march launch, overriding rule and autotuner; 3D
+                                   constant-kappa levels from 64 x 32 x 16 up then all run
+                                   plane marches; 0 (default): rule or autotuner          */
 #define FAS_OPT_TILE 8           /* >= 0: 2D levels of at most this many cells per problem run
                                    their fused passes as block tiles (1..3 sweeps), the
-                                   others as row marches; 0: row marches
+                                   others as row marches (levels below 128 x 64: as one
+                                   kernel per colour phase); 0: row marches
                                    only; default: every level                             */
 #define FAS_OPT_TILE_WAVES 9     /* 6..16: waves per tile workgroup (rows written per tile
                                    4 * waves - 4 nu - 4 in FP64, 8 * waves - 4 nu - 4 in
@@ -113,10 +116,13 @@ extern "C" {
                                    inner_cycles argument, whose correction starts from the full
                                    residual); 0 (default): inner_cycles for all */
 #define FAS_OPT_MARCH3_SWEEPS 14 /* 1 or 2 (default): most sweeps one pass of the 3D plane
-                                   marches runs (constant kappa, levels from 64 x 32 x 16
-                                   up); with 2, V(2, 2) makes one pre- and one post-smoothing
-                                   pass per level instead of two each.  Results are
-                                   identical                                              */
+                                   marches runs (constant kappa); with 2, V(2, 2) makes one
+                                   pre- and one post-smoothing pass per level instead of two
+                                   each.  With 1, every level from 64 x 32 x 16 up runs
+                                   plane marches; with 2, levels too small to fill the
+                                   device with them (up to 192 x 128 x 128 cells in FP64,
+                                   more in batches of levels at most 64 wide) run bricks,
+                                   also one pass each.  Results are identical             */
 
 /* FAS_OPT_ORDER values.  A set is written by the parities of its cells' 1-based indices
  * along x, y (, z), o = odd, e = even:

@@ -71,7 +71,8 @@ class Grid:
         """Solver options (fas_grid_set).  order: smoother set order 'x' (default), 'u' or
         'z'; symmetric: every second sweep in reverse set order (1234-4321); atol: a solve
         also stops once ||rhs - A u||_2 <= atol (0: none); march3_sweeps: most sweeps per
-        3D plane-march pass (1 or 2, the default; identical results)."""
+        3D plane-march pass (1 or 2, the default; identical results).  seg_rows > 0 and
+        march3_sweeps=1 also keep small 3D levels on plane marches instead of bricks."""
         L = load()
         if kmax is not None:
             check(L.fas_grid_set(self.handle, _lib.FAS_OPT_KMAX, float(kmax)), "fas_grid_set")

@@ -85,7 +85,7 @@ int launch_march3_resid(const fas_grid* g, const Coef& c, const void* f, const v
                         double* fpartials);
 
 // Brick passes of small 3D levels (kernels_brick3d.hip): one launch each.  brick_ok: level l
-// takes them, in preference to plane marches.  Arguments as launch_tile_pre / launch_tile_post
+// takes them, in preference to plane marches unless an option of those is set.  Arguments as launch_tile_pre / launch_tile_post
 // (acc64 as u64).
 bool brick_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable);
 // Norm partial sums that a post pass leaves per problem.

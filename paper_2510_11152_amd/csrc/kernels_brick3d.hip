@@ -514,6 +514,8 @@ bool brick_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable)
     // cycles of 384 x 256 x 256 with 6144 bricks there 393 -> 379, of 48 problems of 128^3 with
     // 24576 of 64 columns 1600 -> 1516, of 384^3 with 13824 732 and 746.
     if (fused3_ok(g, l, variable)) {
+        // options of the marches hold for every level that can take one
+        if (g->seg_force || g->march3_ns == 1) return false;
         if (g->dtype == FAS_F32 && l == 0) return blocks <= kBrickMarch32;
         return blocks <= (g->lev[l].n[0] <= 64 ? kBrickMarchNarrow : kBrickMarch);
     }

@@ -85,3 +85,24 @@ def test_tail_holds_every_level_its_budget_admits(lib, f32, variable):
             if want <= L:
                 seen.add(tail_class(g, want))
     assert seen == {0, 1}
+
+
+@pytest.mark.parametrize("n,coarsest", [((64, 32, 16), 4), ((96, 64, 32), 4), ((128, 128, 128), 4)])
+@pytest.mark.parametrize("f32", [False, True])
+def test_march_options_reach_the_levels_that_marches_take(lib, n, coarsest, f32):
+    """Levels from 64 x 32 x 16 up run plane marches when an option of the marches is set: one
+    sweep per pass, or a segment height; smaller levels run bricks all the same."""
+    from paper_2510_11152_amd import _lib as F
+    brick_ok = lib["_ZN3fas8brick_okEPK8fas_gridiiib"]
+    brick_ok.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_bool]
+    brick_ok.restype = ctypes.c_bool
+    with Planned(lib, n, f32, coarsest) as g:
+        def bricks(level):
+            return brick_ok(g, level, 2, 2, False)
+        assert bricks(0) and bricks(1)
+        for opt, value, default in ((F.FAS_OPT_SEG_ROWS, 16, 0), (F.FAS_OPT_MARCH3_SWEEPS, 1, 2)):
+            assert lib.fas_grid_set(g, opt, value) == F.FAS_OK
+            assert not bricks(0), opt
+            assert bricks(1) == (n != (128, 128, 128)), opt  # 64^3 takes marches, 32 x 16 x 8 none
+            assert lib.fas_grid_set(g, opt, default) == F.FAS_OK
+            assert bricks(0) and bricks(1), opt
