@@ -634,12 +634,16 @@ void autotune_level(fas_grid* g, int l, int first, int pre, int post, const void
             return;
         }
     }
-    // 3D: planes per segment.  2D: the rule's rows (one round of waves), half and twice
-    // that, and a few fixed heights.
+    // 3D: planes per segment, the rule's first (0: every pass of the level then goes by its
+    // own rule, so another height has to be faster by more than the timing's noise).  2D: the rule's rows (one round of waves), half and twice that, and a few
+    // fixed heights.
     std::vector<int> cands;
     const int extent = d3 ? g->lev[l].n[2] : g->lev[l].n[1];
+    const int ns3 = d3 ? march3_split(g, pre, rc_in != nullptr, true).back() : 0;
     if (d3) {
-        cands = {8, 16, 32, 64, 128};
+        int planes[fas::kMaxSegCandidates];
+        cands.assign(planes, planes + fas::fused3_seg_candidates(g, l, ns3, planes));
+        cands[0] = 0;
     } else {
         const int rule = fas::fused_seg_rows(g, l, pre);
         for (int r : {rule, (rule / 2 + 1) & ~1, 2 * rule, 64, 128, 256})
@@ -658,8 +662,8 @@ void autotune_level(fas_grid* g, int l, int first, int pre, int post, const void
         for (int rep = 0; rep < 3; ++rep) {
             FAS_HIP_CHECK(hipEventRecord(e0, g->stream));
             if (d3)
-                fas::launch_march3(g, l, g->coef[l], first, 0, march3_split(g, pre, rc_in != nullptr, true).back(), false, f, u,
-                                   scratch, C.u, rc_dst(g, l, pre, post), nullptr);
+                fas::launch_march3(g, l, g->coef[l], first, 0, ns3, false, f, u, scratch, C.u, rc_dst(g, l, pre, post),
+                                   nullptr);
             else if (rc_in)
                 fas::launch_fused_pre(g, l, g->coef[l], first, pre, rc_in, u, scratch, C.u,
                                       rc_dst(g, l, pre, post), g->lev[l].f);
@@ -671,7 +675,7 @@ void autotune_level(fas_grid* g, int l, int first, int pre, int post, const void
             FAS_HIP_CHECK(hipEventElapsedTime(&ms, e0, e1));
             if (rep) total += ms;  // the first launch warms caches
         }
-        if (total < best) {
+        if (total < (best_rows ? 1.f : 0.97f) * best) {
             best = total;
             best_rows = rows;
         }

@@ -68,6 +68,10 @@ void launch_tile_post(const fas_grid* g, int l, const Coef& c, int first, int nu
 bool fused3_ok(const fas_grid* g, int l, bool variable);
 // Norm partial sums that a pass of ns sweeps with a norm leaves per problem on level l.
 int fused3_partials(const fas_grid* g, int l, int ns);
+// Heights of a segment that the autotuner times on level l for passes of ns sweeps, into `out`
+// (their number is returned): first the rule's, one segment fewer and more, then fixed heights.
+constexpr int kMaxSegCandidates = 8;
+int fused3_seg_candidates(const fas_grid* g, int l, int ns, int out[kMaxSegCandidates]);
 // mode 0: sweeps, then uc = R u_out, rc = R(f - A u_out); mode 1: u_in + P(uc - R u_in),
 // then the sweeps; mode 2: the sweeps.  ns = sweeps in the pass (1 or 2).  norm: per-block
 // sums of r^2 (r = f - A u_out) into partials.  fout != nullptr (mode 2, ns 1, no norm): f

@@ -39,6 +39,8 @@
 // instead of storing u.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "fas_device.h"
 #include "fas_fused.h"
 #include "fas_internal.h"
@@ -635,6 +637,19 @@ bool fused3_ok(const fas_grid* g, int l, bool variable)
 {
     if (!g->fused || g->dim != 3 || variable || l >= g->L) return false;
     return g->lev[l].n[0] >= 64 && g->lev[l].n[1] >= 32 && g->lev[l].n[2] >= 16;
+}
+
+int fused3_seg_candidates(const fas_grid* g, int l, int ns, int out[kMaxSegCandidates])
+{
+    const int n2 = g->lev[l].n[2];
+    const int rule = g->dtype == FAS_F64 ? make_args3<double>(g, l, g->coef[l], ns, 0, false).seg_planes
+                                         : make_args3<float>(g, l, g->coef[l], ns, 0, false).seg_planes;
+    const int segs = (n2 + rule - 1) / rule;
+    auto planes = [&](int s) { return s < 1 ? n2 : 2 * ((n2 + 2 * s - 1) / (2 * s)); };
+    int n = 0;
+    for (int p : {rule, planes(segs - 1), planes(segs + 1), 8, 16, 32, 64, 128})
+        if (p >= kMinSegPlanes && p <= n2 && std::find(out, out + n, p) == out + n) out[n++] = p;
+    return n;
 }
 
 int fused3_partials(const fas_grid* g, int l, int ns)

@@ -106,3 +106,29 @@ def test_march_options_reach_the_levels_that_marches_take(lib, n, coarsest, f32)
             assert bricks(1) == (n != (128, 128, 128)), opt  # 64^3 takes marches, 32 x 16 x 8 none
             assert lib.fas_grid_set(g, opt, default) == F.FAS_OK
             assert bricks(0) and bricks(1), opt
+
+
+@pytest.mark.parametrize("n,coarsest", [((64, 32, 16), 4), ((256, 256, 256), 4), ((160, 160, 160), 10), ((512, 512, 512), 4),
+                                        ((64, 64, 20), 10), ((176, 144, 144), 18), ((64, 2048, 640), 4)])
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("sweeps", [1, 2])
+def test_plane_march_autotuner_times_the_rules_height(lib, n, coarsest, f32, sweeps):
+    """The heights that the autotuner times for plane marches start with the rule's, and no
+    height at all takes fewer steps by the rule's count (rounds of blocks over 256 compute
+    units times the planes that a block visits)."""
+    from paper_2510_11152_amd import _lib as F
+    fn = lib["_ZN3fas21fused3_seg_candidatesEPK8fas_gridiiPi"]
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    out = (ctypes.c_int * 8)()
+    with Planned(lib, n, f32, coarsest) as g:
+        assert lib.fas_grid_set(g, F.FAS_OPT_MARCH3_SWEEPS, sweeps) == F.FAS_OK
+        heights = list(out[:fn(g, 0, sweeps, out)])
+    halo = 2 * sweeps + 2
+    tiles = -(-n[0] // (64 - 2 * halo)) * -(-n[1] // ((48 if f32 else 32) - 2 * halo))
+
+    def steps(planes):
+        return -(-tiles * -(-n[2] // planes) // 256) * (planes + halo + 2 * sweeps + 2)
+
+    assert len(heights) >= 2 and len(set(heights)) == len(heights)
+    assert all(4 <= h <= n[2] and h % 2 == 0 for h in heights)
+    assert steps(heights[0]) == min(steps(h) for h in range(4, n[2] + 1, 2))
