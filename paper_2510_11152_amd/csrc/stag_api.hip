@@ -4,6 +4,7 @@
 // layouts.
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <string.h>
 
 #include <algorithm>
 #include <string>
@@ -14,6 +15,26 @@
 
 using fas::Error;
 using namespace fas::stag;
+
+// By bisection over the bit patterns, which have the order of the doubles from 0 to infinity
+// (stepping from (tol / h)^2 takes some 2^60 steps where h sqrt(s2) underflows).
+double fas::stag::s2_limit(double h, double tol)
+{
+    auto stops = [&](uint64_t bits) {
+        double s2;
+        memcpy(&s2, &bits, sizeof s2);
+        return h * sqrt(s2) <= tol;
+    };
+    uint64_t lo = 0, hi = 0x7ff0000000000000;  // infinity
+    if (!stops(lo)) return -1.0;
+    while (hi - lo > 1) {
+        const uint64_t mid = lo + (hi - lo) / 2;
+        (stops(mid) ? lo : hi) = mid;
+    }
+    double s2;
+    memcpy(&s2, &lo, sizeof s2);
+    return s2;
+}
 
 struct fas_stag {
     int loc, cell_bc, coarsest, nuc;
@@ -355,19 +376,6 @@ void check_pointers(const void* f, const void* u)
 bool norm_in_cycle(const fas_stag& S, int nu1, int nu2)
 {
     return S.fused && S.L > 1 && S.tail_top != 0 && nu1 > 0 && launches(nu1) % 2 == 1 && (nu2 == 1 || nu2 == 2);
-}
-
-// The largest s2 with h sqrt(s2) <= tol in double arithmetic (-1: none), so that a test of s2
-// on the device stops at the cycle at which a test of the norm would.
-double s2_limit(double h, double tol)
-{
-    auto stops = [&](double s2) { return h * sqrt(s2) <= tol; };
-    if (!stops(0.0)) return -1.0;
-    double x = (tol / h) * (tol / h);
-    if (!isfinite(x)) x = 1.7976931348623157e308;
-    while (!stops(x)) x = nextafter(x, 0.0);
-    while (x < 1.7976931348623157e308 && stops(nextafter(x, INFINITY))) x = nextafter(x, INFINITY);
-    return x;
 }
 
 // The solve with the stopping test on the device: a result that the host looks at stalls the

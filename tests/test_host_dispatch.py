@@ -2,7 +2,9 @@
 a workspace that nothing touches)."""
 import ctypes
 import itertools
+import math
 import os
+import sys
 
 import pytest
 
@@ -132,3 +134,17 @@ def test_plane_march_autotuner_times_the_rules_height(lib, n, coarsest, f32, swe
     assert len(heights) >= 2 and len(set(heights)) == len(heights)
     assert all(4 <= h <= n[2] and h % 2 == 0 for h in heights)
     assert steps(heights[0]) == min(steps(h) for h in range(4, n[2] + 1, 2))
+
+
+def test_staggered_stopping_limit(lib):
+    """The limit on the squared norm that the device tests is the largest double whose norm
+    passes the host's test, also where h sqrt(s2) underflows."""
+    fn = lib["_ZN3fas4stag8s2_limitEdd"]
+    fn.argtypes, fn.restype = [ctypes.c_double, ctypes.c_double], ctypes.c_double
+    inf, big = math.inf, sys.float_info.max
+    for h in (1e-300, 1e-200, 1e-170, 1e-160, 1e-3, 1 / 3, 1 / 4096, 1.0, 7.0, 1e200):
+        for tol in (0.0, 5e-324, 1e-320, 1e-310, 1e-200, 1e-16, 1e-8, 0.3, 1e150, 1e300, inf):
+            s2 = fn(h, tol)
+            assert 0.0 <= s2 <= big and h * math.sqrt(s2) <= tol, (h, tol)
+            assert s2 == big or h * math.sqrt(math.nextafter(s2, inf)) > tol, (h, tol)
+    assert fn(inf, 1.0) == -1.0
