@@ -16,9 +16,14 @@
 using fas::Error;
 using namespace fas::stag;
 
-// By bisection over the bit patterns, which have the order of the doubles from 0 to infinity
-// (stepping from (tol / h)^2 takes some 2^60 steps where h sqrt(s2) underflows).
-double fas::stag::s2_limit(double h, double tol)
+namespace fas {
+namespace stag {
+
+// The largest finite s2 with h sqrt(s2) <= tol in double arithmetic (-1: none), so that a test
+// of s2 on the device stops at the cycle at which a test of the norm would.  By bisection over
+// the bit patterns, which have the order of the doubles from 0 to infinity (stepping from
+// (tol / h)^2 takes some 2^60 steps where h sqrt(s2) underflows).
+double s2_limit(double h, double tol)
 {
     auto stops = [&](uint64_t bits) {
         double s2;
@@ -35,6 +40,9 @@ double fas::stag::s2_limit(double h, double tol)
     memcpy(&s2, &lo, sizeof s2);
     return s2;
 }
+
+}  // namespace stag
+}  // namespace fas
 
 struct fas_stag {
     int loc, cell_bc, coarsest, nuc;

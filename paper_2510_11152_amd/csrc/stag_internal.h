@@ -92,9 +92,6 @@ struct Status {
 // initial residual, which starts the solve): active while s2 is finite and > s2max.  Does
 // nothing (k > 0) once the solve has stopped.
 void launch_status(hipStream_t s, const double* partials, int n, double s2max, int k, Status* st);
-// The largest finite s2 with h sqrt(s2) <= tol in double arithmetic (-1: none), so that a test
-// of s2 on the device stops at the cycle at which a test of the norm would.
-double s2_limit(double h, double tol);
 // f = r + L u on level L (out of place).
 void launch_form_rhs(hipStream_t s, const Lev& L, const double* r, const double* u, double* f);
 
