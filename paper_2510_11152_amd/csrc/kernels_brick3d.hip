@@ -46,7 +46,6 @@ namespace {
 // Rules of brick_side and brick_ok, in bricks of 8^3 cells over all problems.
 constexpr int64_t kBrickLarge = 768;                        // from here on bricks of 16^3
 constexpr int64_t kBrickMarch = 6144, kBrickMarchNarrow = 24576, kBrickMarch32 = 4096;  // most where marches could run
-constexpr int64_t kBrickSmallMost = 8192;                   // most of 8^3
 
 // Distance (sum over the axes) from a brick up to which a pass reads u: one cell per colour
 // phase, one more for a residual.  f is read one cell less far.
@@ -519,11 +518,25 @@ bool brick_ok(const fas_grid* g, int l, int nu_pre, int nu_post, bool variable)
         if (g->dtype == FAS_F32 && l == 0) return blocks <= kBrickMarch32;
         return blocks <= (g->lev[l].n[0] <= 64 ? kBrickMarchNarrow : kBrickMarch);
     }
-    // Elsewhere whole cycles against the per-level kernels: 1024 problems of 32^3 2388 -> 848 us
-    // (FP64) and 1367 -> 681 (FP32), 48 x 48 x 8192 1430 -> 587, 65536 x 16 x 16 788 -> 496; with
-    // small bricks 8 x 8 x 65536 (8192 of them) 213 -> 206 and 152 -> 148, twice as many the same
-    // or slower.
-    return brick_side(g, l) == 16 || blocks <= kBrickSmallMost;
+    // Elsewhere the per-level kernels are the alternative: their launches cost as much as some
+    // `launches` cells, then their time grows with the cells, that of bricks with the bricks
+    // however empty they are.  Whole cycles, per-level against bricks (us): full bricks, 1024
+    // problems of 32^3 2388 -> 848 (FP64) and 1367 -> 681 (FP32), 48 x 48 x 8192 1430 -> 587,
+    // 8 x 8 x 65536 (8192 small ones) 213 and 206, 152 -> 148; partly filled ones, FP64 / FP32:
+    //   large, a quarter: 4 x 512 x 512 (1024) 136 -> 125 / 114 -> 103, 4 x 32 x 16384 (2048)
+    //     162 and 202 / 143 and 159, 4 x 1024 x 1024 (4096) 278 and 379 / 201 and 288
+    //   large, three eighths: 8 x 12 x 65536 (4096) 373 -> 358 / 270 and 285
+    //   large, a half: 8 x 1024 x 1024 (4096) 462 -> 415 / 332 -> 319, 8 x 2048 x 2048 (16384)
+    //     1845 -> 1614 / 1060 and 1207
+    //   small, a quarter: 4 x 4 x 8192 (1024) 78 -> 71 / 74 -> 63, 4 x 4 x 32768 (4096) 90 and
+    //     134 / 85 and 105
+    //   small, a half: 4 x 8 x 16384 (2048) 91 and 104 / 85 -> 80, 4 x 8 x 65536 153 and 236 /
+    //     140 and 177
+    const bool large = brick_side(g, l) == 16, f32 = g->dtype == FAS_F32;
+    const int64_t cells = large ? (f32 ? 2150 : 1680) : 600;  // that the per-level kernels do in a brick's time
+    const int64_t launches = f32 ? (large ? 1300000 : 800000) : 700000;
+    const int64_t bricks = large ? g->batch * brick_blocks(g, l, 16) : blocks;
+    return bricks * cells <= g->batch * (int64_t)g->lev[l].N + launches;
 }
 
 int brick_partials(const fas_grid* g, int l) { return (int)brick_blocks(g, l, brick_side(g, l)); }

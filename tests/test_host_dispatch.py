@@ -148,3 +148,23 @@ def test_staggered_stopping_limit(lib):
             assert 0.0 <= s2 <= big and h * math.sqrt(s2) <= tol, (h, tol)
             assert s2 == big or h * math.sqrt(math.nextafter(s2, inf)) > tol, (h, tol)
     assert fn(inf, 1.0) == -1.0
+
+
+# (n, coarsest, bricks in FP64, in FP32): levels that bricks fill in part (one or two axes of 4
+# or 8 cells), where many bricks take longer than the per-level kernels, and full ones
+THIN = [((4, 4, 8192), 2, True, True), ((4, 4, 65536), 2, False, False), ((65536, 4, 4), 2, False, False),
+        ((4, 8, 16384), 2, False, True), ((8, 4, 65536), 2, False, False), ((4, 512, 512), 2, True, True),
+        ((4, 1024, 2048), 2, False, False), ((2048, 4, 1024), 2, False, False), ((2048, 2048, 4), 2, False, False),
+        ((8, 12, 32768), 4, True, True), ((8, 12, 131072), 4, False, False), ((8, 2048, 2048), 4, True, False),
+        ((1536, 1536, 8), 4, True, True), ((32, 32, 32), 4, True, True), ((8, 8, 512), 4, True, True),
+        ((16, 1024, 1024), 4, True, True), ((48, 48, 8192), 6, True, True)]
+
+
+@pytest.mark.parametrize("n,coarsest,f64,f32", THIN)
+def test_thin_levels_run_bricks_while_they_are_faster(lib, n, coarsest, f64, f32):
+    brick_ok = lib["_ZN3fas8brick_okEPK8fas_gridiiib"]
+    brick_ok.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_bool]
+    brick_ok.restype = ctypes.c_bool
+    for single, want in ((False, f64), (True, f32)):
+        with Planned(lib, n, single, coarsest) as g:
+            assert brick_ok(g, 0, 2, 2, False) == want, single
