@@ -303,14 +303,20 @@ int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1
         launch_tail(S.stream, S.loc, A);
         return 0;
     }
-    if (r && (nu1 == 0 || l == S.L - 1)) {
-        launch_form_rhs(S.stream, L, r, start, f);  // no pre-smoothing launch to form it in
-        launch_copy(S.stream, start, u, (int64_t)L.nx * L.ny);
-        start = u;
-        r = nullptr;
-    }
     if (l == S.L - 1) {
-        sweeps(S.stream, S.loc, L, f, u, ut, S.nuc, u);  // Remark 1: the coarsest level is smoothed
+        // Remark 1: the coarsest level is smoothed; no pre-smoothing launch forms its f
+        if (!r) {
+            sweeps(S.stream, S.loc, L, f, u, ut, S.nuc, u);
+            return 0;
+        }
+        launch_form_rhs(S.stream, L, r, start, f);
+        const double* from = start;  // u0 stays; the last launch ends in u
+        double* to = launches(S.nuc) % 2 ? u : ut;
+        for (int left = S.nuc; left > 0; left -= left > 1 ? 2 : 1) {
+            launch_sweep(S.stream, S.loc, L, left > 1 ? 2 : 1, f, from, to, SweepIO{}, 0);
+            from = to;
+            to = to == u ? ut : u;
+        }
         return 0;
     }
     auto& C = S.lev[l + 1];
