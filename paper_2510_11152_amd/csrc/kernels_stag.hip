@@ -904,9 +904,9 @@ __global__ __launch_bounds__(256) void k_sum(const double* __restrict__ partials
 // The norm of cycle k and the stopping test (Status).  1024 threads with four loads in flight
 // each: the few thousand sums of a 4096^2 launch took 9.7 us with 256 threads.
 __global__ __launch_bounds__(1024) void k_status(const double* __restrict__ partials, int n, double s2max, int k,
-                                                 Status* __restrict__ st)
+                                                 int* __restrict__ act, Status* host)
 {
-    if (k > 0 && !st->act) return;
+    if (k > 0 && !act[0]) return;
     __shared__ double sh[1024];
     double acc = 0.0;
 #pragma unroll 4
@@ -919,10 +919,12 @@ __global__ __launch_bounds__(1024) void k_status(const double* __restrict__ part
     }
     if (threadIdx.x != 0) return;
     const double s2 = sh[0];
-    const bool finite = isfinite(s2);
-    st->s2 = s2;
-    st->act = finite && s2 > s2max ? 1 : 0;
-    st->cyc = finite ? k : -1 - k;
+    const bool active = isfinite(s2) && s2 > s2max;
+    act[0] = active ? 1 : 0;
+    // (not ordered, as a release to the host would write the L2 back: the host reads s2 once the
+    // stream has ended)
+    __hip_atomic_store(&host->s2, s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&host->seen, status_word(k, active), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ __launch_bounds__(256) void k_copy(const double* __restrict__ src, double* __restrict__ dst, int64_t n)
@@ -1151,9 +1153,9 @@ void launch_form_rhs(hipStream_t s, const Lev& L, const double* r, const double*
     hipLaunchKernelGGL(k_form_rhs, dim3(blocks_for((int64_t)L.nx * L.ny)), dim3(256), 0, s, L, r, u, f);
 }
 
-void launch_status(hipStream_t s, const double* partials, int n, double s2max, int k, Status* st)
+void launch_status(hipStream_t s, const double* partials, int n, double s2max, int k, int* act, Status* host)
 {
-    hipLaunchKernelGGL(k_status, dim3(1), dim3(1024), 0, s, partials, n, s2max, k, st);
+    hipLaunchKernelGGL(k_status, dim3(1), dim3(1024), 0, s, partials, n, s2max, k, act, host);
 }
 
 TailLev tail_lev(const Lev& L)

@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <string>
 
 #include "../../include/fas_stag.h"
@@ -62,10 +63,9 @@ struct fas_stag {
         double* r;        // restricted residual of the finer level (levels >= 1, fused path)
     } lev[fas::kMaxLevels];
     double* partials;
-    double* norm;      // 8 doubles: a norm, or the Status of a solve (device)
-    Status* host;      // pinned copy of the Status, allocated by the first solve that needs it
+    double* norm;      // 8 doubles: a norm, or the active flag of a solve (device)
+    Status* host;      // pinned, allocated by the first solve whose stopping test runs on the device
     const int* act;    // inside such a solve: its active flag, which every launch of a cycle checks
-    int last_cycles, prev_cycles;  // cycles of the last two converged solves (0: none)
     hipStream_t stream;
     // FAS_OPT_PROFILE: HIP events around the finest level's pre- and post-smoothing launches
     int profile;
@@ -278,13 +278,19 @@ double* pre_fused(hipStream_t st, int loc, const Lev& L, const double* r, double
     return const_cast<double*>(a);
 }
 
+// Whether the device has stopped the solve that is running: launches enqueued from here on
+// would do nothing.
+bool over(const fas_stag& S) { return S.act && (__atomic_load_n(&S.host->seen, __ATOMIC_RELAXED) & 1); }
+
 // One V(nu1, nu2) cycle from level l on right-hand side f with the iterate in u (the result
 // returns to u).  r: the level's restricted residual when its right-hand side has yet to be
 // formed (f = r + L u; fused path, levels >= 1; the iterate is then in the level's u0, where
 // the finer level left R u), else null.  Returns the number of residual
-// partial sums the last sweep left in S.partials (0: none, the norm needs its own pass).
+// partial sums the last sweep left in S.partials (0: none, the norm needs its own pass, or the
+// solve is over).
 int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1, int nu2, const double* r = nullptr)
 {
+    if (over(S)) return 0;
     const Lev L = level_op(S, l, a, c);
     double* ut = S.lev[l].ut;
     const double* start = r ? S.lev[l].u0 : u;
@@ -333,6 +339,7 @@ int vcycle(fas_stag& S, int l, double a, double c, double* f, double* u, int nu1
         launch_coarse_rhs(S.stream, level_op(S, l + 1, a, c), C.f, C.u);
         vcycle(S, l + 1, a, c, C.f, C.u, nu1, nu2);
     }
+    if (over(S)) return 0;
     if (S.fused && nu2 > 0) {
         // correction in the first post-smoothing launch, the residual norm (finest level) in
         // the last
@@ -392,44 +399,76 @@ bool norm_in_cycle(const fas_stag& S, int nu1, int nu2)
     return S.fused && S.L > 1 && S.tail_top != 0 && nu1 > 0 && launches(nu1) % 2 == 1 && (nu2 == 1 || nu2 == 2);
 }
 
-// The solve with the stopping test on the device: a result that the host looks at stalls the
-// GPU for tens of microseconds, so after solves that took the same number of cycles that many
-// are enqueued before the first look (the fewer, if the last two solves differ; profiling
-// looks at every cycle).  Cycles enqueued after the stop do nothing, so the iterate, the
-// number of cycles and the norm do not depend on this.  Returns the cycles and the norm.
+// Waits until the device has tested the norm of cycle k, or the solve has stopped, or the
+// stream has nothing left to do; returns whether the solve has stopped.
+bool wait_test(const fas_stag& S, int k)
+{
+    using clock = std::chrono::steady_clock;
+    clock::time_point since = clock::now();
+    for (unsigned spins = 1;; ++spins) {
+        const unsigned w = __atomic_load_n(&S.host->seen, __ATOMIC_RELAXED);
+        if (w & 1) return true;
+        if (w >= status_word(k, true)) return false;
+        if (spins % 64 == 0 && clock::now() - since > std::chrono::milliseconds(2)) {
+            const hipError_t e = hipStreamQuery(S.stream);  // a failed launch never writes the word
+            if (e == hipSuccess) return (__atomic_load_n(&S.host->seen, __ATOMIC_RELAXED) & 1) != 0;
+            if (e != hipErrorNotReady) FAS_HIP_CHECK(e);
+            (void)hipGetLastError();
+            since = clock::now();
+        }
+    }
+}
+
+// The solve with the stopping test on the device.  A result that is copied to the host stalls
+// the GPU for tens of microseconds, so each test writes its result to pinned memory, which does
+// not, and the host stays one cycle ahead of the last test it has seen, so that the GPU always
+// has work: except where the last two norms let it expect the stop after the cycle that runs,
+// whose end it then waits for.  A stop it did not expect costs what was enqueued of the cycle
+// after it, launches that do nothing, so the iterate, the number of cycles and the norm do not
+// depend on this.  Profiling waits for every cycle.  Returns the cycles and the norm.
 void solve_looped(fas_stag& S, double a, double c, const double* f, double* u, double tol, int nu1, int nu2, int kmax,
                   int& k_out, double& res_out)
 {
     if (!S.host) FAS_HIP_CHECK(hipHostMalloc((void**)&S.host, sizeof(Status), hipHostMallocDefault));
-    Status* const dev = reinterpret_cast<Status*>(S.norm);
+    Status* host = nullptr;
+    FAS_HIP_CHECK(hipHostGetDevicePointer((void**)&host, S.host, 0));
+    __atomic_store_n(&S.host->seen, 0u, __ATOMIC_RELAXED);
+    int* const act = reinterpret_cast<int*>(S.norm);
     const double s2max = s2_limit(S.h, tol);
     const Lev L = level_op(S, 0, a, c);
-    launch_status(S.stream, S.partials, launch_resnorm_partials(S.stream, L, f, u, nullptr, S.partials), s2max, 0, dev);
+    launch_status(S.stream, S.partials, launch_resnorm_partials(S.stream, L, f, u, nullptr, S.partials), s2max, 0, act,
+                  host);
     struct Gate {
         fas_stag& S;
         ~Gate() { S.act = nullptr; }
     } gate{S};
-    S.act = &dev->act;
-    const int horizon = S.profile ? 0 : std::min(S.last_cycles, S.prev_cycles);
-    S.prev_cycles = S.last_cycles;
-    S.last_cycles = 0;
+    S.act = act;
+    double before = 0.0;  // the norm squared of the cycle before the last one tested
+    auto ends = [&](int k) {  // with k cycles enqueued, k - 1 of them tested: stopped, or about to
+        if (wait_test(S, k - 1)) return true;
+        double s2;
+        __atomic_load(&S.host->s2, &s2, __ATOMIC_RELAXED);
+        const bool last = k > 1 && s2 * (s2 / before) <= s2max;
+        before = s2;
+        return last;
+    };
     int k = 0;
     for (;; ++k) {
-        if (k >= horizon || k >= kmax) {
-            FAS_HIP_CHECK(hipMemcpyAsync(S.host, dev, sizeof(Status), hipMemcpyDeviceToHost, S.stream));
+        if (S.profile || k >= kmax || (k > 0 && ends(k))) {
             FAS_HIP_CHECK(hipStreamSynchronize(S.stream));
             profile_collect(S);
-            if (!S.host->act || k >= kmax) break;
+            if ((__atomic_load_n(&S.host->seen, __ATOMIC_RELAXED) & 1) || k >= kmax) break;
         }
         const int nb = vcycle(S, 0, a, c, const_cast<double*>(f), u, nu1, nu2);
-        if (nb <= 0) throw Error(FAS_ERR_ARG, "internal: a cycle without its norm");
-        launch_status(S.stream, S.partials, nb, s2max, k + 1, dev);
+        if (nb > 0)
+            launch_status(S.stream, S.partials, nb, s2max, k + 1, act, host);
+        else if (!over(S))
+            throw Error(FAS_ERR_ARG, "internal: a cycle without its norm");
     }
-    // (still active at kmax: every cycle enqueued ran)
-    if (!S.host->act) k = S.host->cyc < 0 ? -1 - S.host->cyc : S.host->cyc;
-    k_out = k;
+    // the stream has ended, and with it the last test that ran
+    if (!S.host->seen) throw Error(FAS_ERR_HIP, "the stopping test did not run");
+    k_out = (int)(S.host->seen / 2) - 1;
     res_out = S.h * sqrt(S.host->s2);
-    if (res_out <= tol) S.last_cycles = k;
 }
 
 int solve(fas_stag& S, double a, double c, const double* f, double* u, double tol, int nu1, int nu2, int kmax,

@@ -82,16 +82,20 @@ int launch_sweep(hipStream_t s, int loc, const Lev& L, int nu, const double* f, 
                  const SweepIO& io, unsigned flags);
 // Blocks of such a launch (tiles_x may be NULL).
 int sweep_blocks(const Lev& L, int nu, unsigned flags, int* tiles_x);
-// State of a solve whose stopping test runs on the device.
+// What the host sees of a solve whose stopping test runs on the device (pinned host memory,
+// written by the device after each test).
 struct Status {
-    double s2;  // ||f - L u||^2 after the last cycle that ran
-    int act;    // 1: still iterating
-    int cyc;    // cycles of the stop, or -1 - cycles if the norm is not finite
+    double s2;      // ||f - L u||^2 after the last cycle that ran
+    unsigned seen;  // status_word of that cycle (0: before the first test)
 };
+__host__ __device__ constexpr unsigned status_word(int k, bool active)
+{
+    return 2u * ((unsigned)k + 1u) + (active ? 0u : 1u);
+}
 // s2 = sum of partials[0 .. n) in a fixed order, then the stopping test after cycle k (0: the
-// initial residual, which starts the solve): active while s2 is finite and > s2max.  Does
-// nothing (k > 0) once the solve has stopped.
-void launch_status(hipStream_t s, const double* partials, int n, double s2max, int k, Status* st);
+// initial residual, which starts the solve): act (device memory) is 1 while s2 is finite and
+// > s2max.  Does nothing (k > 0) once the solve has stopped.
+void launch_status(hipStream_t s, const double* partials, int n, double s2max, int k, int* act, Status* host);
 // f = r + L u on level L (out of place).
 void launch_form_rhs(hipStream_t s, const Lev& L, const double* r, const double* u, double* f);
 
