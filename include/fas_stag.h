@@ -13,7 +13,12 @@
  *   - nx and ny must both be coarsest * 2^L with L >= 1 (coarsest >= 2): every level
  *     halves both axes, down to `coarsest` cells on the shorter axis.
  *   - Every call is enqueued on the stream given at creation (NULL: the default stream).
- *     Calls that report a residual or a cycle count wait for that stream.
+ *     Calls that report a residual or a cycle count wait for that stream.  A solve's
+ *     stopping test runs on the device; the host enqueues one cycle ahead of the last test
+ *     whose result it has seen.
+ *   - The library allocates no device memory.  A handle's own runtime objects are a small
+ *     pinned host buffer (results of the stopping test, allocated by the first solve) and
+ *     HIP events (FAS_OPT_PROFILE), released with the handle.
  *   - Two handles must not run on one workspace at the same time.
  */
 #ifndef FAS_STAG_H

@@ -326,7 +326,7 @@ void smooth(fas_grid* g, int l, const void* f, void* u, int sweeps, bool reverse
 // FAS V-cycle below level l (Alg. 1 with the coarse steps replaced by recursion).
 // partials != nullptr asks the finest-level post-smoothing to leave per-tile residual
 // partial sums there; returns the number written (0 if it could not).
-// rc_in (level >= 1, march levels only): the restricted residual from which the first pass
+// rc_in (level >= 1, fused levels only): the restricted residual from which the first pass
 // forms f itself.
 void autotune_level(fas_grid* g, int l, int first, int pre, int post, const void* f, const void* u,
                     const void* rc_in = nullptr, void* scratch = nullptr);
@@ -334,8 +334,8 @@ void autotune_level(fas_grid* g, int l, int first, int pre, int post, const void
 void autotune_tile(fas_grid* g, int l, int first, int pre, int post, const void* f, const void* u,
                    const void* rc_in);
 
-// Whether coarse level lc forms its FAS right-hand side inside its first march pass (2D
-// strips or 3D planes); the finer level then leaves R(f - A u) in lev[lc].r (the pass
+// Whether coarse level lc forms its FAS right-hand side inside its first fused pass (2D tiles
+// or strips, 3D bricks or plane marches); the finer level then leaves R(f - A u) in lev[lc].r (the pass
 // reads it while writing f, so it cannot be f itself).
 // Sweeps of each 3D march pass of one smoothing step of nu sweeps, in order: up to
 // march3_ns each.  pre: the step ends with the residual-restriction pass, which takes the

@@ -93,8 +93,8 @@ struct BrickShape {
 };
 
 // The blocks, the brick's own first, the others in the order of memory: v = i | j << 4 | k << 8
-// | distance << 12; of large bricks w = LDS index | index of the block below << 12 (32-bit
-// entries: above << 12 more).
+// | distance << 12; of large bricks also the LDS indices of the block and of those below and
+// above it.
 template <int R, int BS>
 struct BrickList {
     using B = BrickShape<R, BS>;
